@@ -10,12 +10,15 @@ Prints one JSON line:
                 summed over the N virtual ranks; the per-rank figure is
                 bus_gbps_per_rank); t = the mean of the timed operations, each
                 bracketed by its own HIP events (the median is reported too)
-* roofline   -- the dominant kernel's own rate: the algorithmic bytes of its
-                launches / their durations, from a HIP event pair recorded on
-                the kernels' stream around every launch of the first three
-                timed operations; against the 8 TB/s HBM3E peak; traffic from
-                the committed rocprofv3 counter summary when it matches the
-                current kernel source
+* roofline   -- the dominant kernel's own rate against the 8 TB/s HBM3E peak;
+                traffic from the committed rocprofv3 counter summary when it
+                matches the current kernel source.  An operation that runs as
+                one walk launch: the bytes it cannot do without (each input
+                read once, each output written once) / the operation's time.
+                Else the algorithmic bytes of the kernel's launches / their
+                durations, from the library's launch trace
+* step_schedule -- for a walked operation: the same schedule run step by step,
+                three traced operations after the timed ones
 * cpu_baseline -- the CPU oracle timed in the same process: the threaded C++
                 oracle over the whole operation on every host CPU, inputs
                 regenerated from the seed (reduce-scatter: PAT association and
@@ -64,8 +67,24 @@ WORKLOADS = {
         "PAT all-gather, N=128 virtual ranks, fp32 N(0,1), 262144-element (1 MiB) chunk per rank"),
 }
 
-KERNEL_SOURCES = ["paper_2506_20252_amd/csrc/kernels.hip", "paper_2506_20252_amd/csrc/kernels.hpp",
-                  "paper_2506_20252_amd/csrc/device_types.hpp"]
+_CSRC = "paper_2506_20252_amd/csrc/"
+KERNEL_SOURCES = {
+    "step": [_CSRC + f for f in ("kernels.hip", "device_access.hpp", "kernels.hpp", "device_types.hpp")],
+    "walk": [_CSRC + f for f in ("walk.hip", "walk.hpp", "device_access.hpp")],
+}
+
+
+def runs_as_walk(coll, count, mode):
+    """Whether the library runs such an operation as one walk launch (its rule
+    for stream mode at the default settings; this file sets no step-kernel
+    tuning variable outside the sweeps)."""
+    return mode == "stream" and coll == "rs" and count >= 16 and os.environ.get("PAT_WALK") != "0"
+
+
+def needed_bytes(coll, n, count, dtype):
+    """Each input byte read once, each output byte written once."""
+    chunk = count * (2 if dtype == "bfloat16" else 4)
+    return float(n * n * chunk + n * chunk)
 
 
 def _code_only(text):
@@ -93,31 +112,32 @@ def _code_only(text):
     return "".join(out)
 
 
-def kernel_source_hash():
+def kernel_source_hash(family="step"):
     """Hash of the kernel sources' code (comments and whitespace ignored), so
     that counter summaries stay valid across comment edits only."""
     h = hashlib.sha256()
-    for rel in KERNEL_SOURCES:
+    for rel in KERNEL_SOURCES[family]:
         with open(os.path.join(ROOT, rel)) as f:
             h.update(_code_only(f.read()).encode())
     return h.hexdigest()[:16]
 
 
 def committed_traffic(workload_id, mode, kernel):
-    """HBM-side bytes per launch of `kernel` (step_kernel / tree_kernel) from
+    """HBM-side bytes per launch of `kernel` (step_kernel / tree_kernel / a walk kernel) from
     the committed counter summary, if it was taken on the current kernel
     source; else None.  Stream and graph modes launch the same kernels; the
     persistent kernel has no summary."""
     if mode == "persistent":
         return None
-    kind = "tree_kernel" if kernel.startswith("tree_kernel") else "step_kernel"
+    kind = next((k for k in ("tree_kernel", "walk_kernel") if kernel.startswith(k.split("_")[0])), "step_kernel")
+    family = "walk" if kind == "walk_kernel" else "step"
     path = os.path.join(ROOT, "profiles", f"traffic_{kind}_workload{workload_id}.txt")
     if not os.path.exists(path):
         return None
     text = open(path).read()
     m_hash = re.search(r"kernel_source_hash:\s*(\w+)", text)
     m_bytes = re.search(r"hbm_bytes_per_launch:\s*([0-9.eE+]+)", text)
-    if not m_hash or not m_bytes or m_hash.group(1) != kernel_source_hash():
+    if not m_hash or not m_bytes or m_hash.group(1) != kernel_source_hash(family):
         return None
     return float(m_bytes.group(1))
 
@@ -242,7 +262,8 @@ def small_size_latency(reps=200):
         out[f"{coll}_us"] = round(mean_ms * 1e3, 2)
         out[f"{coll}_median_us"] = round(statistics.median(per) * 1e3, 2)
         out["steps"] = info["steps"]
-        out[f"{coll}_launches"] = info["launches_per_op"]  # the far fusable steps run as one launch
+        walked = runs_as_walk("rs" if coll == "reducescatter" else "ag", count, "stream")
+        out[f"{coll}_launches"] = 1 if walked else info["launches_per_op"]
         del send, recv, S, R
     torch.cuda.empty_cache()
     return out
@@ -251,7 +272,7 @@ def small_size_latency(reps=200):
 def other_workloads(reps=50):
     """Workloads 1-3 timed the same way (HIP events around back-to-back
     operations): microseconds per operation, aggregate bus bandwidth and the
-    fraction of HBM peak that the algorithmic bytes reach.  Last, workload 3
+    fraction of HBM peak that the bytes it cannot do without reach.  Last, workload 3
     with one element fewer per chunk: rows that are only element-aligned and
     chunks that end in a partial vector, the relaxed 128-bit kernels' case."""
     import torch
@@ -292,11 +313,12 @@ def other_workloads(reps=50):
         pat.check(pat.pat_check_device_status(stream))
         sec = mean_ms / 1e3
         st, info = pat.pat_plan_info(code, n, count, dtype)
+        walked = runs_as_walk(coll, count, "stream")
         rows.append({"workload": desc, "us": round(sec * 1e6, 2), "median_us": round(statistics.median(per) * 1e3, 2),
                      "steps": info["steps"],
-                     "launches": info["launches_per_op"],
+                     "launches": 1 if walked else info["launches_per_op"],
                      "bus_gbps": round(n * info["bus_bytes_per_rank"] / sec / 1e9, 2),
-                     "hbm_frac_alg": round(info["alg_bytes"] / sec / 1e9 / HBM_PEAK_GBPS, 4)})
+                     "hbm_frac": round(needed_bytes(coll, n, count, dtype) / sec / 1e9 / HBM_PEAK_GBPS, 4)})
         del send, recv, S, R
     torch.cuda.empty_cache()
     return rows
@@ -457,7 +479,9 @@ def budget_sweep(wid, reps, max_slot_bytes=32 << 30, aggregation="pow2"):
     the plan goes from one linear tree (N - 1 steps) to ceil(log2 N) steps,
     stopping early once the slots of all ranks would exceed max_slot_bytes.
     With aggregation "budget" the budget also takes 3, 5, 6 and 7 chunks
-    (K chunks per step, the list schedule where it is shorter)."""
+    (K chunks per step, the list schedule where it is shorter).  PAT_WALK=0:
+    a walk launch does not depend on the budget."""
+    os.environ["PAT_WALK"] = "0"
     import torch
 
     import synth
@@ -532,7 +556,7 @@ def budget_sweep(wid, reps, max_slot_bytes=32 << 30, aggregation="pow2"):
 def size_sweep(n=128, max_input_bytes=16 << 30, reps_bytes=32 << 30):
     """Both collectives at one rank count over chunk sizes from 256 B up, at
     the default budget: microseconds per operation, steps and launches, bus
-    bandwidth and the fraction of HBM peak that the algorithmic bytes reach --
+    bandwidth and the fraction of HBM peak that the needed bytes reach --
     where the latency regime ends and the bandwidth roofline begins.  float32
     reduce-scatter and all-gather, N(0,1) inputs, seed 0x5153."""
     import torch
@@ -577,10 +601,11 @@ def size_sweep(n=128, max_input_bytes=16 << 30, reps_bytes=32 << 30):
             pat.check(pat.pat_check_device_status(stream))
             sec = e0.elapsed_time(e1) / 1e3 / reps
             rows.append({"collective": "reduce-scatter" if coll == "rs" else "all-gather", "chunk_bytes": count * 4,
-                         "T": info["T"], "steps": info["steps"], "launches": info["launches_per_op"],
-                         "streaming": bool(info["streaming"]), "us": round(sec * 1e6, 2),
+                         "T": info["T"], "steps": info["steps"],
+                         "launches": 1 if runs_as_walk(coll, count, "stream") else info["launches_per_op"],
+                         "us": round(sec * 1e6, 2),
                          "bus_gbps": round(n * info["bus_bytes_per_rank"] / sec / 1e9, 1),
-                         "hbm_frac_alg": round(info["alg_bytes"] / sec / 1e9 / HBM_PEAK_GBPS, 4)})
+                         "hbm_frac": round(needed_bytes(coll, n, count, "float32") / sec / 1e9 / HBM_PEAK_GBPS, 4)})
             print(json.dumps(rows[-1]), file=sys.stderr, flush=True)
             del send, recv, S, R
             pat.check(pat.pat_finalize())
@@ -676,10 +701,10 @@ def kernel_name(coll, dtype, path, streaming, kind):
 
 
 def kernel_roofline(info, coll, dtype, reps):
-    """The launch trace of the first `reps` timed operations: a HIP event pair
-    around every kernel launch, recorded by the library on the kernels' stream
-    (armed before the timed region), and each launch's algorithmic bytes from
-    the plan's byte model.  The dominant kernel is the one with the most traced
+    """The launch trace of `reps` operations: a HIP event pair around every
+    kernel launch, recorded by the library on the kernels' stream (armed before
+    the operations), and each launch's algorithmic bytes from the plan's byte
+    model.  The dominant kernel is the one with the most traced
     time; its rate is its launches' bytes over their summed durations."""
     from paper_2506_20252_amd import pat
     launches = info["launches_per_op"]
@@ -716,8 +741,8 @@ def kernel_roofline(info, coll, dtype, reps):
                         "median": round(statistics.median(rates) / HBM_PEAK_GBPS, 4),
                         "max": round(rates[-1] / HBM_PEAK_GBPS, 4)},
         "traced_ops": reps,
-        "timing": f"HIP event pair around each launch of the first {reps} timed operations, on the kernels' "
-                  "stream (library launch trace)",
+        "timing": f"HIP event pair around each launch of {reps} operations, on the kernels' stream (library "
+                  "launch trace)",
         "kernels": kinds,
     }
 
@@ -876,20 +901,34 @@ def main():
     torch.cuda.synchronize()
     pat.check(pat.pat_check_device_status(stream))
 
-    # The launch trace covers the first operations of the timed region: an
-    # event pair around each launch adds a few microseconds per launch, so
-    # tracing all of them would slow the timed operations measurably (1% on
-    # workload 5, 16% on workload 4); three traced operations of twenty cost
-    # the mean under 0.2% on workload 5.
-    traced = min(args.steps, 3, (1 << 20) // max(1, info["launches_per_op"]))
-    if args.mode == "stream":
-        pat.check(pat.pat_trace_start(traced * info["launches_per_op"]))
     ms, rep_ms = time_ops(op, stream, args.steps)
     pat.check(pat.pat_check_device_status(stream))
     sec = ms / 1e3
     bus_per_rank = info["bus_bytes_per_rank"]
+    # The launch trace measures the step schedule, launch by launch, after the
+    # timed operations: a traced operation runs its steps, and the event pairs
+    # slow it by a few microseconds per launch.  One untraced operation first
+    # loads the step kernels.
+    step_roof = None
     if args.mode == "stream":
-        roof = kernel_roofline(info, coll, dtype, traced)
+        asked = os.environ.get("PAT_WALK")
+        os.environ["PAT_WALK"] = "0"
+        pat.check(op(), "steps")
+        os.environ.pop("PAT_WALK") if asked is None else os.environ.update(PAT_WALK=asked)
+        traced = min(args.steps, 3, (1 << 20) // max(1, info["launches_per_op"]))
+        pat.check(pat.pat_trace_start(traced * info["launches_per_op"]))
+        for _ in range(traced):
+            pat.check(op(), "traced")
+        torch.cuda.synchronize()
+        step_roof = kernel_roofline(info, coll, dtype, traced)
+    walked = runs_as_walk(coll, count, args.mode)
+    if walked:
+        need = needed_bytes(coll, n, count, dtype)
+        roof = {"kernel": f"walk_{coll}_kernel", "achieved": need / sec / 1e9, "launches_per_op": 1,
+                "avg_launch_us": round(ms * 1e3, 3), "bytes_per_launch": need,
+                "timing": "HIP events around the timed operations, one launch each"}
+    elif args.mode == "stream":
+        roof = step_roof
     else:
         # no per-launch trace in these modes: the operation's time spread over its launches
         launches = 1 if args.mode == "persistent" else info["launches_per_op"]
@@ -922,16 +961,19 @@ def main():
                    "collective": "reduce-scatter" if coll == "rs" else "all-gather", "exec_mode": args.mode,
                    "buffer_bytes_per_slot": pat.pat_get_buffer_bytes(), "T": info["T"],
                    "pat_steps": info["steps"], "pieces": info["pieces"],
-                   "fused_steps": 0 if args.mode == "persistent" else info["fused_steps"],
+                   "walk": walked, "fused_steps": 0 if args.mode == "persistent" else info["fused_steps"],
                    "streaming_accesses": bool(info["streaming"]), "xcd_run": info["xcd_run"],
                    "seed": seed},
         "bus_gbps_per_rank": round(bus_per_rank / sec / 1e9, 4),
         "latency_us": round(ms * 1e3, 2),
-        "alg_bytes_per_op": info["alg_bytes"],
-        "hbm_frac_alg": round(info["alg_bytes"] / sec / 1e9 / HBM_PEAK_GBPS, 4),
+        "schedule_bytes_per_op": info["alg_bytes"],
+        "needed_bytes_per_op": needed_bytes(coll, n, count, dtype),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic, **roof},
     }
+    if walked:
+        out["step_schedule"] = {**step_roof, "achieved": round(step_roof["achieved"], 2),
+                                "frac": round(step_roof["achieved"] / HBM_PEAK_GBPS, 4)}
     if not args.no_latency:
         out["small_size_latency"] = small_size_latency()
         out["other_workloads"] = other_workloads()
@@ -944,7 +986,8 @@ def main():
     torch.cuda.empty_cache()
     if not args.no_ceiling:
         ceil = streaming_ceiling()
-        shape_key = "rs_shape_gbps" if coll == "rs" else "ag_shape_gbps"
+        shape_key = ({"rs": "read_gbps", "ag": "write_gbps"} if walked else
+                     {"rs": "rs_shape_gbps", "ag": "ag_shape_gbps"})[coll]
         ceil["roofline_achieved_over_" + shape_key] = round(achieved / ceil[shape_key], 4)
         out["streaming_ceiling"] = ceil
     print(json.dumps(out), flush=True)

@@ -92,9 +92,10 @@ typedef enum {
   /* One kernel per step, captured once per plan (and vector width) into a
    * HIP graph and replayed. */
   PAT_EXEC_GRAPH = 1,
-  /* One kernel per step, launched directly on the stream.  The default: as
-   * fast as the graph for large operations, and without the graph launch's
-   * fixed cost for small ones. */
+  /* Launched directly on the stream.  The default.  An operation runs as one
+   * walk launch where pat_set_top_fusion says so, else one kernel per step
+   * (and a fused range): as fast as the graph for large operations, and
+   * without the graph launch's fixed cost for small ones. */
   PAT_EXEC_STREAM = 2,
   /* Dataflow: one launch per piece, no step barrier.  Workgroups take work
    * in step order as in the persistent mode, but a work item (one tile of
@@ -140,8 +141,8 @@ pat_status_t pat_reducescatter(const void* const* sendbufs, void* const* recvbuf
  * device memory: code under HIP graph capture, tight serving loops, harnesses
  * that forbid allocation.  Same operation, arguments, summation order, buffer
  * budget, linear order and fusion settings as pat_reducescatter, and the same
- * bits; it always runs as per-step kernels on `stream` (the execution-mode
- * setting does not apply).
+ * bits; it always runs as stream mode does (the execution-mode setting does
+ * not apply).
  *
  * Instead of the plan cache's device memory, every table, intermediate buffer
  * and float32 root accumulator lives in a fixed array of
@@ -233,6 +234,18 @@ int pat_get_exec_mode(void);
  * fuses the whole fusable range whenever it has two or more steps.  Neither
  * fuses a chunk that is split into pieces.  A tile is the smallest power of
  * two from 32 to 256 vectors that keeps the launch within 1024 workgroups.
+ *
+ * AUTO in stream mode goes further: a far-first reduce-scatter of at most 4096
+ * ranks and at least 16 elements per chunk runs as one walk launch.  Each lane
+ * walks the whole tree (or an aligned part of it) of one 16-byte vector in the
+ * linear order of section "The PAT algorithm", so that the one chunk per
+ * distance the linear walk needs to hold is a register: each input is read
+ * once, and no partial goes through memory.  The summation order is the
+ * same; the buffer budget, pieces and the aggregation rule, which shape the
+ * step schedule, do not change a walk.  The step schedule runs instead while a
+ * launch trace is armed, for plans with a step clock, and when the environment
+ * has PAT_WALK=0 or one of the step kernels' tuning variables (PAT_TREE_*,
+ * PAT_XCD_GRAIN, PAT_STREAMING, PAT_PIECE_PIPELINE).
  */
 typedef enum { PAT_FUSION_AUTO = 0, PAT_FUSION_OFF = 1, PAT_FUSION_ON = 2 } pat_fusion_t;
 pat_status_t pat_set_top_fusion(int mode);
@@ -244,7 +257,8 @@ int pat_get_top_fusion(void);
  * the operation's result is then undefined. */
 pat_status_t pat_set_barrier_timeout_us(uint32_t microseconds);
 
-/* Plan summary.  Host-only: needs no GPU. */
+/* Plan summary: the step schedule of a plan (also where operations run as a
+ * walk launch).  Host-only: needs no GPU. */
 typedef struct {
   int nranks;
   int L;                      /* ceil(log2 nranks) */
@@ -266,8 +280,8 @@ typedef struct {
   size_t slot_bytes_total;    /* all ranks, plus the float32 root accumulators */
   double alg_bytes;           /* memory bytes the steps must read + write per operation */
   double bus_bytes_per_rank;  /* (nranks - 1) * count * sizeof(dtype) */
-  int fused_steps;            /* steps run as one fused launch (stream/graph modes, current setting) */
-  int launches_per_op;        /* kernel launches per operation in stream mode (path vector_path) */
+  int fused_steps;            /* steps the schedule runs as one fused launch (stream/graph modes, current setting) */
+  int launches_per_op;        /* kernel launches the schedule takes per operation in stream mode (path vector_path) */
   int streaming;              /* 1: nontemporal loads and stores (operations of >= 1e9 algorithmic bytes) */
   int xcd_run;                /* step kernels: each XCD takes runs of this many consecutive work items
                                  (0: a contiguous eighth of each step; all-gather 0, reduce-scatter 32) */
@@ -298,8 +312,9 @@ pat_status_t pat_plan_steps(pat_collective_t coll, int nranks, size_t count, pat
                             int* nentries);
 
 /*
- * Launch tracing, for measurement (stream mode only; graph and persistent
- * modes and pat_reducescatter_noalloc record nothing).  pat_trace_start
+ * Launch tracing of the step schedule, for measurement (stream mode only; graph
+ * and persistent modes and pat_reducescatter_noalloc record nothing).  While a
+ * trace is armed, operations run their steps, never a walk launch.  pat_trace_start
  * creates 2 * max_launches HIP events and arms the trace: the following
  * operations record one event on their stream right before and one right
  * after each kernel launch, until max_launches launches are recorded.
@@ -318,8 +333,8 @@ pat_status_t pat_trace_read(float* ms, double* bytes, int32_t* kind, int32_t* st
 
 /*
  * Step clock of fused launches (measurement; stream mode).  When the
- * environment variable PAT_STEP_CLOCK is 1 as a plan is made, every fused
- * launch of that plan (the range of steps one workgroup per (tree, tile) runs
+ * environment variable PAT_STEP_CLOCK is 1 as a plan is made, that plan's
+ * operations run their steps, and every fused launch of it (the range of steps one workgroup per (tree, tile) runs
  * with workgroup barriers in between) records, per workgroup, the device wall
  * clock before its first step and after each step: step k of workgroup w took
  * stamps[w * per_workgroup + k + 1] - stamps[w * per_workgroup + k] ticks

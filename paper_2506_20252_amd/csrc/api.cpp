@@ -1,5 +1,6 @@
 // C-ABI of the PAT library: argument checks, plan cache, execution modes.
 #include <hip/hip_runtime.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <atomic>
@@ -16,6 +17,7 @@
 #include "../../include/pat.h"
 #include "kernels.hpp"
 #include "plan.hpp"
+#include "walk.hpp"
 
 namespace {
 
@@ -759,6 +761,45 @@ double launch_bytes(const HostPlan& h, int vi, int s) {
   return pat::step_bytes(d, s % nexec, std::min<int64_t>(d.piece_elems, d.count - e0));
 }
 
+// Whether the environment asks for the step schedule's launches: PAT_WALK=0,
+// or one of the step kernels' own tuning variables is set.
+bool step_schedule_asked() {
+  static const char* const names[] = {"WALK=0",          "TREE_TILE=", "TREE_FUSE_VECS=", "TREE_FUSE_BYTES=",
+                                      "TREE_EDGE_CACHE=", "XCD_GRAIN=", "STREAMING=",      "PIECE_PIPELINE="};
+  for (char** e = environ; *e; ++e) {
+    if (std::strncmp(*e, "PAT_", 4)) continue;
+    for (const char* n : names)
+      if (!std::strncmp(*e + 4, n, std::strlen(n))) return true;
+  }
+  return false;
+}
+
+// Walk launches read inputs and write outputs with nontemporal accesses from
+// this many bytes of input on (the 256 MB Infinity Cache then no longer keeps
+// an operation's input for the next one).
+// Measured on MI355X, cached / nontemporal: N=128 float32, 4 KiB chunks (67
+// MB) 12.5 / 14.5 us; N=64 bf16, 32 KiB chunks (134 MB) 24.2 / 22.8 us.
+constexpr double kWalkStreamingBytes = 1e8;
+
+// Whether an operation runs as one walk launch instead of the step schedule:
+// the far-first summation order (a walk adds in no other, and that one does
+// not depend on the budget, the pieces or the aggregation rule), sizes a walk
+// is the faster one for, and nothing that asks for the schedule's own
+// launches.
+bool walk_applies(const HostPlan& h) {
+  const pat::PlanDesc& d = h.desc;
+  return d.coll == 1 && d.order == pat::kFarFirst && d.count >= pat::kWalkLeastElems && d.N <= pat::kWalkMostRanks &&
+         !d.pipelined && fusion_now() == PAT_FUSION_AUTO && !step_schedule_asked();
+}
+
+hipError_t enqueue_walk(const HostPlan& h, pat_dtype_t dt, int vi, const pat::KCtx& cx, hipStream_t q) {
+  const pat::PlanDesc& d = h.desc;
+  const double input = double(d.N) * d.N * double(d.count) * d.esize_in;
+  pat::TreeRange tr{};
+  tr.walk = 1;
+  return pat::launch_tree(variant_for(d.coll, dt, vi), input >= kWalkStreamingBytes, cx, tr, q);
+}
+
 // Stream-mode launch sequence: one kernel per step, except that the fused
 // range (steps whose slot entries each serve one tree) runs as one launch.
 // With a trace, each launch is bracketed by its event pair on `q`.
@@ -944,6 +985,8 @@ pat_status_t run(int coll, const void* const* send, void* const* recv, size_t co
         std::fprintf(stderr, "[pat] persistent launch: capacity=%d cus=%d grid=%d steps=%d\n",
                      capacity, plan->cus, grid, cx.nsteps);
     HIP_TRY(pat::launch_persistent(var, nt, cx, grid, stream));
+  } else if (mode == PAT_EXEC_STREAM && !g_trace.armed && !plan->step_clock && walk_applies(h)) {
+    HIP_TRY(enqueue_walk(h, dt, vi, cx, stream));
   } else {
     const pat::TreeRange tr = tree_range(h, vi);
     if (mode == PAT_EXEC_STREAM && plan->step_clock && tr.s1 > tr.s0) {
@@ -1069,7 +1112,8 @@ pat_status_t run_noalloc(int coll, const void* const* send, void* const* recv, s
   }
   const HostPlan& h = ss.plan;
   const int vi = path_for(h, vec);
-  if (ss.vi != vi) {
+  const bool walk = walk_applies(h);
+  if (!walk && ss.vi != vi) {  // a walk reads the pointer tables only
     ss.vi = -1;
     const auto& entries = h.desc.entries;
     if (!entries.empty())
@@ -1092,7 +1136,7 @@ pat_status_t run_noalloc(int coll, const void* const* send, void* const* recv, s
                                 (const pat::DevEntry*)(base + ss.off_entries),
                                 (const pat::DevStep*)(base + ss.off_steps), count, N,
                                 needs_own_copy(coll, send, recv, N, chunk));
-  HIP_TRY(enqueue_stream(h, coll, dt, vi, cx, tree_range(h, vi), stream));
+  HIP_TRY(walk ? enqueue_walk(h, dt, vi, cx, stream) : enqueue_stream(h, coll, dt, vi, cx, tree_range(h, vi), stream));
   return PAT_OK;
 }
 

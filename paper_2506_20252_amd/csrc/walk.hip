@@ -1,0 +1,350 @@
+// Walk kernels for gfx950 (CDNA4): a whole operation as one launch, every
+// tree walked in its linear order with the intermediate buffers in registers.
+//
+// The step kernels run the schedule one step of all trees at a time, and a
+// partial or a forwarded chunk goes through memory between two steps: about
+// three transfers of a chunk per edge, where each input has to be read only
+// once.  The far-first linear walk of one tree (section "The PAT algorithm")
+// needs one chunk of intermediate buffer per distance, ceil(log2 N) in all;
+// over one 16-byte vector of the chunk that is a few registers, so a lane can
+// walk its vector's whole tree by itself.
+//
+// Reduce-scatter: lane (R, v) owns vector v of destination chunk R.  It reads
+// the tree's positions q = 0 .. N - 1 (rank R + q) in order and adds them as
+// the reversed binomial tree does: the partial S(lo, w) of the sub-tree that
+// starts at position lo and spans w positions is S(lo, w/2), or, where
+// position lo + w/2 exists, S(lo, w/2) + S(lo + w/2, w/2) -- the order in
+// which the schedule adds children, nearest first, whatever the number of
+// parallel sub-trees, pieces or chunks per step.
+
+#include <hip/hip_runtime.h>
+
+#include "device_access.hpp"
+#include "walk.hpp"
+
+namespace pat {
+namespace {
+
+struct WalkCtx {
+  const void* const* send;  // [N] device pointers (device table)
+  void* const* recv;        // [N]
+  int64_t chunk_bytes;      // of a user chunk
+  int64_t V;                // 16-byte vectors per chunk, a partial last one among them
+  int32_t N;
+  int32_t back;             // a partial last vector begins this many elements inside the one before (0: none)
+  int32_t w;                // positions per lane group, a power of two
+  int32_t lanes;            // vectors per workgroup, a multiple of 64
+  uint32_t tiles, blocks;   // workgroups per chunk (a workgroup's vectors in one chunk), in all
+  uint32_t grain;           // consecutive blocks per XCD
+};
+
+// A chunk's vectors are read at element alignment (see Access); the last one
+// may be moved back to end where the chunk ends.
+struct WI32 {
+  using in_t = v4u;
+  static constexpr int kElem = 4, kElems = 4;
+  struct acc_t {
+    v4u a;
+  };
+  __device__ static acc_t widen(const in_t& x) { return {x}; }
+  __device__ static in_t narrow(const acc_t& x) { return x.a; }
+  __device__ static acc_t add(const acc_t& x, const acc_t& y) { return {x.a + y.a}; }  // wraps
+};
+
+struct WF32 {
+  using in_t = v4f;
+  static constexpr int kElem = 4, kElems = 4;
+  struct acc_t {
+    v4f a;
+  };
+  __device__ static acc_t widen(const in_t& x) { return {x}; }
+  __device__ static in_t narrow(const acc_t& x) { return x.a; }
+  __device__ static acc_t add(const acc_t& x, const acc_t& y) { return {x.a + y.a}; }
+};
+
+struct WB16 {
+  using in_t = v4u;  // 8 bf16, element 2j in the low half of word j
+  static constexpr int kElem = 2, kElems = 8;
+  struct acc_t {
+    v4f a, b;
+  };
+  __device__ static acc_t widen(const in_t& x) {
+    return {v4f{bf16_lo(x.x), bf16_hi(x.x), bf16_lo(x.y), bf16_hi(x.y)},
+            v4f{bf16_lo(x.z), bf16_hi(x.z), bf16_lo(x.w), bf16_hi(x.w)}};
+  }
+  __device__ static in_t narrow(const acc_t& x) {
+    return v4u{bf16_rne(x.a.x) | (bf16_rne(x.a.y) << 16), bf16_rne(x.a.z) | (bf16_rne(x.a.w) << 16),
+               bf16_rne(x.b.x) | (bf16_rne(x.b.y) << 16), bf16_rne(x.b.z) | (bf16_rne(x.b.w) << 16)};
+  }
+  __device__ static acc_t add(const acc_t& x, const acc_t& y) { return {x.a + y.a, x.b + y.b}; }
+};
+
+// Partials of complete sub-trees, one per distance, like the schedule's slots:
+// entry l holds a sub-tree of 2^l leaves (a leaf being whatever push() is
+// given).  Every index is a compile-time constant and every branch uniform,
+// so the entries stay in registers.
+template <class T, int LV>
+struct WalkSlots {
+  typename T::acc_t st[LV];
+
+  // Leaf number b (0, 1, ...): merges with the sub-trees it completes.
+  template <int L = 0>
+  __device__ __forceinline__ void push(int b, const typename T::acc_t& x) {
+    if constexpr (L < LV) {
+      if ((b >> L) & 1)
+        push<L + 1>(b, T::add(st[L], x));
+      else
+        st[L] = x;
+    }
+  }
+
+  // The tree of nb >= 1 leaves: the truncated tree's complete sub-trees, the
+  // smallest (last) first.
+  template <int L = 0>
+  __device__ __forceinline__ typename T::acc_t total(int nb, typename T::acc_t x = {}, bool any = false) const {
+    if constexpr (L < LV) {
+      if ((nb >> L) & 1) {
+        x = any ? T::add(st[L], x) : st[L];
+        any = true;
+      }
+      return total<L + 1>(nb, x, any);
+    } else {
+      return x;
+    }
+  }
+};
+
+// Tree sum of the group's first m leaves (1 <= m <= G).
+template <class T, int G>
+__device__ __forceinline__ typename T::acc_t group_sum(const typename T::in_t (&x)[G], int m) {
+  typename T::acc_t a[G];
+  if (m == G) {
+#pragma unroll
+    for (int j = 0; j < G; ++j) a[j] = T::widen(x[j]);
+#pragma unroll
+    for (int d = 1; d < G; d *= 2)
+#pragma unroll
+      for (int j = 0; j < G; j += 2 * d) a[j] = T::add(a[j], a[j + d]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < G; ++j)
+      if (j < m) a[j] = T::widen(x[j]);
+#pragma unroll
+    for (int d = 1; d < G; d *= 2)
+#pragma unroll
+      for (int j = 0; j < G; j += 2 * d)
+        if (j + d < m) a[j] = T::add(a[j], a[j + d]);
+  }
+  return a[0];
+}
+
+// Reduce-scatter.  A workgroup owns `lanes` vectors, blockDim / lanes = S
+// lane groups to each: group s walks positions [s w, (s + 1) w), the sub-tree
+// of span w (a power of two) that starts there, and the first group adds the S
+// partials by the same rule through LDS.  `lanes` is a multiple of 64, so a
+// wave's lanes share s and every loop below is uniform.  UNI: a workgroup's
+// vectors belong to one chunk, whose senders' addresses are then scalar; else
+// they are consecutive vectors of consecutive chunks.
+//
+// A lane reads G positions at a time and has the next G on the way while it
+// adds.  The bound is HBM's read rate.  Measured on MI355X, step schedule ->
+// walk: N=64 float32 1 MiB 1992 -> 654 us, N=128 bf16 4 MiB 52.6 -> 11.7 ms
+// (6.7 and 5.9 TB/s of input), N=1000 float32 256 B 139 -> 76 us a call.
+template <class T, int G, int MAXT, int LV, bool SPLIT, bool UNI, bool NT>
+__global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkCtx cx) {
+  using in_t = typename T::in_t;
+  using acc_t = typename T::acc_t;
+  const int N = cx.N;
+  const int lanes = SPLIT ? cx.lanes : MAXT;
+  int s = 0, lane = threadIdx.x;
+  if constexpr (SPLIT) {
+    s = __builtin_amdgcn_readfirstlane(threadIdx.x / lanes);
+    lane = threadIdx.x - s * lanes;
+  }
+  // Workgroups go to the 8 XCDs round-robin; each XCD takes runs of `grain`
+  // consecutive blocks.
+  const uint32_t x8 = blockIdx.x % 8, j8 = blockIdx.x / 8;
+  const uint32_t blk = (j8 / cx.grain) * 8 * cx.grain + x8 * cx.grain + j8 % cx.grain;
+  if (blk >= cx.blocks) return;
+  int R;
+  int64_t v;
+  bool live;
+  if constexpr (UNI) {
+    R = (int)(blk / cx.tiles);
+    v = (int64_t)(blk - (uint32_t)R * cx.tiles) * lanes + lane;
+    live = v < cx.V;
+  } else {
+    const int64_t f = (int64_t)blk * lanes + lane;
+    const int64_t vecs = cx.N * cx.V;
+    live = f < vecs;
+    if (vecs < (int64_t(1) << 31)) {
+      R = (int)((uint32_t)f / (uint32_t)cx.V);
+      v = (uint32_t)f - (uint32_t)R * (uint32_t)cx.V;
+    } else {
+      R = (int)(f / cx.V);
+      v = f - (int64_t)R * cx.V;
+    }
+  }
+  const bool part = cx.back && v == cx.V - 1;
+  const int64_t voff = v * 16 - (part ? cx.back * T::kElem : 0);
+  const int64_t soff = (int64_t)R * cx.chunk_bytes + voff;
+
+  acc_t sum;
+  const int p0 = SPLIT ? s * cx.w : 0;
+  const int n = SPLIT && N - p0 > cx.w ? cx.w : N - p0;  // positions of this lane group
+  if (live && n > 0) {
+    auto load = [&](in_t(&x)[G], int q, int m) {
+      const char* p[G];
+#pragma unroll
+      for (int j = 0; j < G; ++j)
+        if (j < m) p[j] = (const char*)cx.send[wrap_add(R, p0 + q + j, N)];
+#pragma unroll
+      for (int j = 0; j < G; ++j)
+        if (j < m) x[j] = ldg<in_t, NT, T::kElem>(p[j] + soff);
+    };
+    const int groups = (n + G - 1) / G;
+    auto size = [&](int g) { return n - g * G < G ? n - g * G : G; };
+    WalkSlots<T, LV> slots;
+    in_t x[G], y[G];
+    load(x, 0, size(0));
+    for (int g = 0; g < groups; g += 2) {
+      const bool two = g + 1 < groups;
+      if (two) load(y, (g + 1) * G, size(g + 1));
+      slots.push(g, group_sum<T, G>(x, size(g)));
+      if (two) {
+        if (g + 2 < groups) load(x, (g + 2) * G, size(g + 2));
+        slots.push(g + 1, group_sum<T, G>(y, size(g + 1)));
+      }
+    }
+    sum = slots.total(groups);
+  }
+  if constexpr (SPLIT) {
+    __shared__ acc_t partial[MAXT];
+    if (live && n > 0) partial[threadIdx.x] = sum;
+    __syncthreads();
+    if (s > 0 || !live) return;
+    const int parts = (N + cx.w - 1) / cx.w;
+    WalkSlots<T, 5> top;  // at most 16 partials
+    top.push(0, sum);
+    for (int u = 1; u < parts; ++u) top.push(u, partial[u * lanes + lane]);
+    sum = top.total(parts);
+  } else {
+    if (!live) return;
+  }
+  const in_t out = T::narrow(sum);
+  char* const dst = (char*)cx.recv[R] + voff;
+  if (part)
+    stg_from<NT, T::kElem>(dst, out, cx.back);
+  else
+    stg<NT, T::kElem>(dst, out);
+}
+
+// Grid of `blocks` workgroups in XCD runs of cx.grain.
+dim3 walk_grid(const WalkCtx& cx) {
+  const uint64_t run = 8ull * cx.grain;
+  return dim3((unsigned)((cx.blocks + run - 1) / run * run));
+}
+
+template <class T, int G, int MAXT, int LV, bool SPLIT, bool NT>
+void launch_walk_rs_k(const WalkCtx& cx, bool uni, int threads, hipStream_t stream) {
+  if (uni)
+    hipLaunchKernelGGL((walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, NT>), walk_grid(cx), dim3(threads), 0, stream, cx);
+  else
+    hipLaunchKernelGGL((walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, NT>), walk_grid(cx), dim3(threads), 0, stream,
+                       cx);
+}
+
+// Slots of a lane group: the sub-tree it walks spans at most 2^(slots - 1)
+// groups of positions.
+template <class T>
+constexpr int walk_slots(int S) {
+  return S <= 4 ? 6 : T::kElem == 2 ? 7 : 8;
+}
+// Positions read at a time.  A whole tree: 4.  A part of one: float32 and
+// int32 2 (56 VGPRs with a chunk's own workgroups, 8 waves per SIMD), bf16 4.
+template <class T>
+constexpr int walk_group(int S) {
+  return S == 1 || T::kElem == 2 ? 4 : 2;
+}
+
+// S: lane groups per vector.  One reads a whole tree where that alone gives
+// enough waves: kWalkWaves, about what the chip holds at once.  Fewer leave
+// HBM waiting, more cost an LDS exchange per vector and shorter walks.  A
+// group keeps at least kWalkSpan positions (two rounds of loads), and at most
+// what its slots hold.  Measured on MI355X, us at S = 1, 2, 4, 8, 16 (waves at
+// S = 1): N=64 bf16 32 KiB (2048) 28, 22, 23, 29, 31; N=50 float32 20 KB (976)
+// 24, 18, 12, 10.3, 13; N=500 float32 1200 B (586) -, -, 77, 56, 67; N=128
+// float32 4 KiB (512) 37, 20, 13, 12.5, 13.6.
+//
+// Order of the workgroups: each XCD takes runs of `grain` consecutive blocks,
+// whose rows then cover its L2's channels evenly; one by one, blocks of 1 KiB
+// per row keep an XCD on the same few channels (N=64 bf16 32 KiB at S = 4: 35
+// against 23 us).  Long runs also keep an XCD on fewer pages: N=128 bf16 4 MiB
+// 13.9 ms one by one, 10.8, 10.6, 10.5, 10.4 ms with runs of 4, 16, 64, 256;
+// short ones leave a small grid balanced (N=300 float32 4 KiB, 1200 blocks: 75
+// us with runs of 4, 126 with 64).
+constexpr int64_t kWalkWaves = 4096;
+constexpr int kWalkSpan = 8;
+constexpr int kWalkMostGroups = 16;
+
+template <class T, bool NT>
+hipError_t launch_walk_rs_t(WalkCtx cx, hipStream_t stream) {
+  int span = 1;
+  while (span < cx.N) span *= 2;
+  const int64_t waves = (cx.N * cx.V + 63) / 64;
+  auto holds = [&](int S) { return span / S <= walk_group<T>(S) << (walk_slots<T>(S) - 1); };
+  int S = 1;
+  while (S < kWalkMostGroups && ((waves * S < kWalkWaves && span / S > kWalkSpan) || !holds(S))) S *= 2;
+  if (!holds(S)) return hipErrorInvalidValue;
+  const int threads = S <= 4 ? 256 : 64 * S;
+  cx.lanes = threads / S;
+  cx.w = span / S;
+  const int64_t tiles = (cx.V + cx.lanes - 1) / cx.lanes;
+  // A chunk's vectors fill its own workgroups unless that leaves too many lanes idle.
+  const bool uni = tiles * cx.lanes <= cx.V + cx.V / 8;
+  const int64_t blocks = uni ? tiles * cx.N : (cx.N * cx.V + cx.lanes - 1) / cx.lanes;
+  if (blocks > (int64_t(1) << 30)) return hipErrorInvalidValue;
+  cx.tiles = (uint32_t)tiles;
+  cx.blocks = (uint32_t)blocks;
+  cx.grain = blocks >= 16384 ? 64 : 4;
+  if (S == 1)
+    launch_walk_rs_k<T, walk_group<T>(1), 256, walk_slots<T>(1), false, NT>(cx, uni, threads, stream);
+  else if (S <= 4)
+    launch_walk_rs_k<T, walk_group<T>(4), 256, walk_slots<T>(4), true, NT>(cx, uni, threads, stream);
+  else
+    launch_walk_rs_k<T, walk_group<T>(16), 1024, walk_slots<T>(16), true, NT>(cx, uni, threads, stream);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+template <class T>
+hipError_t launch_walk_rs(const WalkCtx& cx, bool streaming, hipStream_t stream) {
+  return streaming ? launch_walk_rs_t<T, true>(cx, stream) : launch_walk_rs_t<T, false>(cx, stream);
+}
+
+hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, hipStream_t stream) {
+  const int64_t per = 16 / cx.esize;
+  if (cx.count < kWalkLeastElems || cx.N > kWalkMostRanks) return hipErrorInvalidValue;
+  WalkCtx wx{};
+  wx.send = cx.send;
+  wx.recv = cx.recv;
+  wx.N = cx.N;
+  wx.chunk_bytes = cx.count * cx.esize;
+  wx.V = (cx.count + per - 1) / per;
+  wx.back = (int32_t)(wx.V * per - cx.count);
+  switch (v) {  // whichever path the plan's pieces take: a walk has none
+    case kRsI32S:
+    case kRsI32Vec:
+    case kRsI32VecU: return launch_walk_rs<WI32>(wx, streaming, stream);
+    case kRsF32S:
+    case kRsF32Vec:
+    case kRsF32VecU: return launch_walk_rs<WF32>(wx, streaming, stream);
+    case kRsB16S:
+    case kRsB16Vec:
+    case kRsB16VecU: return launch_walk_rs<WB16>(wx, streaming, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace pat

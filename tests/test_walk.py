@@ -1,0 +1,152 @@
+"""Walk launches (stream mode, AUTO fusion): a whole operation in one launch.
+
+Sizes sit where the launch changes shape: one lane group per vector or several
+(2, 4: 256 lanes; 8, 16: 64 per group), a remainder of a group's positions,
+truncated parts, chunks that fill a workgroup or share one, a partial last
+vector, the smallest chunk and the largest rank count a walk is taken for and
+the first beyond.  Bar: the same bits as the CPU oracle's PAT order, and as the
+step kernels (fusion off) on the same inputs.
+"""
+
+import os
+import re
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import native
+from paper_2506_20252_amd import build as B
+from paper_2506_20252_amd import pat
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+TORCH = {"int32": torch.int32, "float32": torch.float32, "bfloat16": torch.bfloat16}
+DIST = {"int32": "int32_pm2p20", "float32": "f32_normal", "bfloat16": "bf16_normal"}
+WIDTH = {"int32": np.uint32, "float32": np.uint32, "bfloat16": np.uint16}
+
+
+def bits(t):
+    if t.dtype == torch.bfloat16:
+        return t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+    return t.contiguous().cpu().numpy().view(np.uint32)
+
+
+def rows(n, elems, dtype, layout):
+    """N rows of `elems` elements: rows of one tensor, rows one element off a
+    16-byte boundary with a gap between them, or N allocations."""
+    dev = torch.device("cuda:0")
+    if layout == "separate":
+        return [torch.empty(elems, dtype=TORCH[dtype], device=dev) for _ in range(n)]
+    skew, gap = (1, 3) if layout == "skewed" else (0, 0)
+    flat = torch.empty(n * (elems + gap) + skew, dtype=TORCH[dtype], device=dev)
+    return [flat[skew + r * (elems + gap): skew + r * (elems + gap) + elems] for r in range(n)]
+
+
+@pytest.fixture(scope="module")
+def walk_asm(tmp_path_factory):
+    if not os.path.exists(B.hipcc()):
+        pytest.skip("hipcc not available")
+    out = tmp_path_factory.mktemp("asm") / "walk.s"
+    flags = [f for f in B.HIPCC_FLAGS if f not in ("-fPIC", "-shared")]
+    cmd = [B.hipcc(), *flags, "--cuda-device-only", "-S", "-I", os.path.join(ROOT, "include"),
+           os.path.join(B.CSRC, "walk.hip"), "-o", str(out)]
+    res = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert res.returncode == 0, res.stderr[-2000:]
+    return out.read_text()
+
+
+def test_walk_kernels_keep_their_slots_in_registers(walk_asm):
+    """No scratch memory, no packed fp32; VGPRs within what a workgroup's
+    declared size allows (512 per SIMD lane: 128 at 1024 lanes)."""
+    names = re.findall(r"^\s+\.name:\s+(\S+)$", walk_asm, re.M)
+    priv = [int(x) for x in re.findall(r"^\s+\.private_segment_fixed_size:\s+(\d+)$", walk_asm, re.M)]
+    vgpr = [int(x) for x in re.findall(r"^\s+\.vgpr_count:\s+(\d+)$", walk_asm, re.M)]
+    assert names and len(names) == len(priv) == len(vgpr)
+    assert not [(n, p) for n, p in zip(names, priv) if p]
+    assert not [(n, v) for n, v in zip(names, vgpr) if v > 128]
+    assert not re.search(r"\bv_pk_(add|mul|fma)_f32\b", walk_asm)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,count,dtype,layout", [
+    (2, 16, "float32", "rows"), (3, 17, "bfloat16", "skewed"), (5, 1000, "int32", "separate"),
+    (8, 4096, "float32", "rows"), (9, 4095, "bfloat16", "rows"), (16, 1024, "float32", "skewed"),
+    (13, 70001, "bfloat16", "rows"), (64, 16384, "float32", "rows"), (65, 1023, "float32", "separate"),
+    (128, 8191, "float32", "rows"), (127, 129, "bfloat16", "skewed"), (129, 2049, "int32", "rows"),
+    (200, 520, "float32", "rows"), (257, 250, "bfloat16", "rows"), (300, 75, "float32", "skewed"),
+    (513, 67, "float32", "rows"), (1000, 64, "float32", "rows"), (1025, 33, "bfloat16", "rows"),
+    (2049, 16, "float32", "rows"), (4096, 18, "bfloat16", "rows"), (4097, 16, "bfloat16", "rows"),
+    (31, 15, "float32", "rows"),
+])
+@pytest.mark.parametrize("entry", ["reducescatter", "reducescatter_noalloc"])
+def test_walked_reducescatter(n, count, dtype, layout, entry):
+    seed = 0x3A1C + 7 * n + count
+    print(f"[gpu] walk {entry} n={n} count={count} {dtype} {layout} seed={seed:#x}", file=sys.stderr, flush=True)
+    st, info = pat.pat_plan_info(pat.PAT_REDUCESCATTER, n, count, dtype)
+    if entry == "reducescatter_noalloc" and info["slot_bytes_total"] > 200 << 20:
+        entry = "reducescatter"
+    stream = torch.cuda.current_stream()
+    pat.check(pat.pat_set_exec_mode("stream"))
+    send, recv = rows(n, n * count, dtype, layout), rows(n, count, dtype, layout)
+    for x in range(n):
+        synth.fill(send[x], DIST[dtype], seed, x)
+    S, R = pat.pointer_array(send), pat.pointer_array(recv)
+    outs = []
+    for fusion in ("auto", "off"):
+        for r in recv:
+            r.view(torch.uint8).fill_(0xA5) if r.data_ptr() % 4 == 0 else r.fill_(1)
+        pat.check(pat.pat_set_top_fusion(fusion))
+        try:
+            pat.check(getattr(pat, "pat_" + entry)(S, R, count, dtype, pat.PAT_SUM, n, stream))
+            torch.cuda.synchronize()
+        finally:
+            pat.check(pat.pat_set_top_fusion("auto"))
+        outs.append(np.stack([bits(r) for r in recv]))
+    np.testing.assert_array_equal(outs[0], outs[1])
+    want = native.reducescatter(dtype, n, count, dist=DIST[dtype], seed=seed)["pat"]
+    np.testing.assert_array_equal(outs[0], want.view(WIDTH[dtype]).reshape(n, count))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,count,dtype", [(7, 1001, "float32"), (40, 203, "bfloat16"), (12, 64, "int32")])
+def test_walked_reducescatter_in_place_and_special_values(n, count, dtype):
+    """In place (rank r receives into its own chunk r), with infinities, NaN,
+    negative zeros and subnormals among the inputs: the step kernels' bits
+    (any NaN for a NaN), and send buffers otherwise untouched."""
+    print(f"[gpu] walk in place n={n} count={count} {dtype}", file=sys.stderr, flush=True)
+    pat.check(pat.pat_set_exec_mode("stream"))
+    stream = torch.cuda.current_stream()
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    src = torch.empty((n, n * count), dtype=TORCH[dtype], device="cuda:0")
+    if dtype == "int32":
+        src.random_(-(1 << 31), 1 << 31, generator=gen)
+    else:
+        src.normal_(generator=gen)
+        for k, v in enumerate((float("inf"), float("-inf"), float("nan"), -0.0, 1e-40)):
+            src[k % n, k::17] = v
+        src[:, 3::29] = -0.0
+    got = []
+    for fusion in ("auto", "off"):
+        send = src.clone()
+        pat.check(pat.pat_set_top_fusion(fusion))
+        try:
+            pat.check(pat.pat_reducescatter(list(send), [send[r, r * count:] for r in range(n)], count, dtype,
+                                            pat.PAT_SUM, n, stream))
+            torch.cuda.synchronize()
+        finally:
+            pat.check(pat.pat_set_top_fusion("auto"))
+        got.append(send)
+    for r in range(n):  # only chunk r of row r may change
+        for t in got:
+            same = torch.ones(n * count, dtype=torch.bool, device="cuda:0")
+            same[r * count:(r + 1) * count] = False
+            assert torch.equal(t[r][same].view(torch.uint8), src[r][same].view(torch.uint8))
+    a, b = (t.clone() for t in got)
+    if dtype != "int32":
+        assert torch.equal(a.isnan(), b.isnan())
+        a[a.isnan()] = 0
+        b[b.isnan()] = 0
+    assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
