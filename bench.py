@@ -78,7 +78,7 @@ def runs_as_walk(coll, count, mode):
     """Whether the library runs such an operation as one walk launch (its rule
     for stream mode at the default settings; this file sets no step-kernel
     tuning variable outside the sweeps)."""
-    return mode == "stream" and coll == "rs" and count >= 16 and os.environ.get("PAT_WALK") != "0"
+    return mode == "stream" and (coll == "ag" or count >= 16) and os.environ.get("PAT_WALK") != "0"
 
 
 def needed_bytes(coll, n, count, dtype):

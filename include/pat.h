@@ -235,17 +235,20 @@ int pat_get_exec_mode(void);
  * fuses a chunk that is split into pieces.  A tile is the smallest power of
  * two from 32 to 256 vectors that keeps the launch within 1024 workgroups.
  *
- * AUTO in stream mode goes further: a far-first reduce-scatter of at most 4096
- * ranks and at least 16 elements per chunk runs as one walk launch.  Each lane
- * walks the whole tree (or an aligned part of it) of one 16-byte vector in the
- * linear order of section "The PAT algorithm", so that the one chunk per
- * distance the linear walk needs to hold is a register: each input is read
- * once, and no partial goes through memory.  The summation order is the
- * same; the buffer budget, pieces and the aggregation rule, which shape the
- * step schedule, do not change a walk.  The step schedule runs instead while a
- * launch trace is armed, for plans with a step clock, and when the environment
- * has PAT_WALK=0 or one of the step kernels' tuning variables (PAT_TREE_*,
- * PAT_XCD_GRAIN, PAT_STREAMING, PAT_PIECE_PIPELINE).
+ * AUTO in stream mode goes further: an operation runs as one walk launch, in
+ * which no intermediate buffer is in memory.  A far-first reduce-scatter of at
+ * most 4096 ranks and at least 16 elements per chunk: each lane walks the whole
+ * tree (or an aligned part of it) of one 16-byte vector in the linear order of
+ * section "The PAT algorithm", so that the one chunk per distance the linear
+ * walk needs to hold is a register, and each input is read once.  An all-gather
+ * (either linear order): each lane reads one vector of the concatenation once
+ * and stores it to several ranks, as every node of a chunk's tree forwards the
+ * bytes it received.  Results and the summation order are the same; the buffer
+ * budget, pieces and the aggregation rule, which shape the step schedule, do
+ * not change a walk.  The step schedule runs instead while a launch trace is
+ * armed, for plans with a step clock, and when the environment has PAT_WALK=0
+ * or one of the step kernels' tuning variables (PAT_TREE_*, PAT_XCD_GRAIN,
+ * PAT_STREAMING, PAT_PIECE_PIPELINE).
  */
 typedef enum { PAT_FUSION_AUTO = 0, PAT_FUSION_OFF = 1, PAT_FUSION_ON = 2 } pat_fusion_t;
 pat_status_t pat_set_top_fusion(int mode);
@@ -314,7 +317,8 @@ pat_status_t pat_plan_steps(pat_collective_t coll, int nranks, size_t count, pat
 /*
  * Launch tracing of the step schedule, for measurement (stream mode only; graph
  * and persistent modes and pat_reducescatter_noalloc record nothing).  While a
- * trace is armed, operations run their steps, never a walk launch.  pat_trace_start
+ * trace is armed, operations run their steps, never a walk launch.
+ * pat_trace_start
  * creates 2 * max_launches HIP events and arms the trace: the following
  * operations record one event on their stream right before and one right
  * after each kernel launch, until max_launches launches are recorded.
@@ -334,8 +338,8 @@ pat_status_t pat_trace_read(float* ms, double* bytes, int32_t* kind, int32_t* st
 /*
  * Step clock of fused launches (measurement; stream mode).  When the
  * environment variable PAT_STEP_CLOCK is 1 as a plan is made, that plan's
- * operations run their steps, and every fused launch of it (the range of steps one workgroup per (tree, tile) runs
- * with workgroup barriers in between) records, per workgroup, the device wall
+ * operations run their steps, and every fused launch of it (the range of steps
+ * one workgroup per (tree, tile) runs with workgroup barriers in between) records, per workgroup, the device wall
  * clock before its first step and after each step: step k of workgroup w took
  * stamps[w * per_workgroup + k + 1] - stamps[w * per_workgroup + k] ticks
  * (*ticks_per_us per microsecond).  pat_step_clock waits for the plan's last

@@ -782,21 +782,25 @@ bool step_schedule_asked() {
 constexpr double kWalkStreamingBytes = 1e8;
 
 // Whether an operation runs as one walk launch instead of the step schedule:
-// the far-first summation order (a walk adds in no other, and that one does
-// not depend on the budget, the pieces or the aggregation rule), sizes a walk
-// is the faster one for, and nothing that asks for the schedule's own
-// launches.
+// an all-gather, or a reduce-scatter in the far-first summation order (a walk
+// adds in no other, and that one does not depend on the budget, the pieces or
+// the aggregation rule) of sizes a walk is the faster one for, and nothing
+// that asks for the schedule's own launches.
 bool walk_applies(const HostPlan& h) {
   const pat::PlanDesc& d = h.desc;
-  return d.coll == 1 && d.order == pat::kFarFirst && d.count >= pat::kWalkLeastElems && d.N <= pat::kWalkMostRanks &&
-         !d.pipelined && fusion_now() == PAT_FUSION_AUTO && !step_schedule_asked();
+  if (d.coll == 1 &&
+      (d.order != pat::kFarFirst || d.count < pat::kWalkLeastElems || d.N > pat::kWalkMostRanks))
+    return false;
+  return !d.pipelined && fusion_now() == PAT_FUSION_AUTO && !step_schedule_asked();
 }
 
-hipError_t enqueue_walk(const HostPlan& h, pat_dtype_t dt, int vi, const pat::KCtx& cx, hipStream_t q) {
+hipError_t enqueue_walk(const HostPlan& h, pat_dtype_t dt, int vi, const pat::KCtx& cx, void* const* recv,
+                        hipStream_t q) {
   const pat::PlanDesc& d = h.desc;
   const double input = double(d.N) * d.N * double(d.count) * d.esize_in;
   pat::TreeRange tr{};
   tr.walk = 1;
+  tr.walk_recv_stride = (int64_t)((uintptr_t)recv[1] - (uintptr_t)recv[0]);
   return pat::launch_tree(variant_for(d.coll, dt, vi), input >= kWalkStreamingBytes, cx, tr, q);
 }
 
@@ -986,7 +990,7 @@ pat_status_t run(int coll, const void* const* send, void* const* recv, size_t co
                      capacity, plan->cus, grid, cx.nsteps);
     HIP_TRY(pat::launch_persistent(var, nt, cx, grid, stream));
   } else if (mode == PAT_EXEC_STREAM && !g_trace.armed && !plan->step_clock && walk_applies(h)) {
-    HIP_TRY(enqueue_walk(h, dt, vi, cx, stream));
+    HIP_TRY(enqueue_walk(h, dt, vi, cx, recv, stream));
   } else {
     const pat::TreeRange tr = tree_range(h, vi);
     if (mode == PAT_EXEC_STREAM && plan->step_clock && tr.s1 > tr.s0) {
@@ -1136,7 +1140,7 @@ pat_status_t run_noalloc(int coll, const void* const* send, void* const* recv, s
                                 (const pat::DevEntry*)(base + ss.off_entries),
                                 (const pat::DevStep*)(base + ss.off_steps), count, N,
                                 needs_own_copy(coll, send, recv, N, chunk));
-  HIP_TRY(walk ? enqueue_walk(h, dt, vi, cx, stream) : enqueue_stream(h, coll, dt, vi, cx, tree_range(h, vi), stream));
+  HIP_TRY(walk ? enqueue_walk(h, dt, vi, cx, recv, stream) : enqueue_stream(h, coll, dt, vi, cx, tree_range(h, vi), stream));
   return PAT_OK;
 }
 

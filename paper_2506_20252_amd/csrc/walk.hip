@@ -19,6 +19,9 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <type_traits>
+
 #include "device_access.hpp"
 #include "walk.hpp"
 
@@ -316,6 +319,144 @@ hipError_t launch_walk_rs_t(WalkCtx cx, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// All-gather
+// ---------------------------------------------------------------------------
+
+// Every receive row is the same concatenation of the N chunks, and every node
+// of a chunk's tree forwards the bytes it received: a workgroup takes 256
+// 16-byte vectors of the concatenation (a tile) and a few receivers, reads the
+// tile once, into registers, and stores it to each receiver in turn.
+struct GatherCtx {
+  const void* const* send;  // [N] device pointers (device table)
+  void* const* recv;        // [N]
+  int64_t chunk_bytes;
+  int64_t row_bytes;        // N * chunk_bytes
+  int32_t N;
+  int32_t period;           // rows r and r + period start at the same offset from a 128-byte line
+  int32_t run;              // receivers per workgroup, `period` apart
+  uint32_t tiles, blocks;   // tiles per row, workgroups in all
+  uint32_t grain;           // consecutive blocks per XCD
+};
+
+constexpr int kGatherThreads = 256;
+constexpr int kGatherTile = kGatherThreads * 16;  // bytes
+
+// The bound is HBM's write rate.  A tile's vectors start where the
+// workgroup's first receiver has a 128-byte line, so that its stores write
+// whole lines also where rows start in the middle of one (then the first tile
+// begins before the row): N=1000 ranks of 63 float32, rows 96 bytes past the
+// line before's end, 39 us against 56 us with every tile at a multiple of 4096
+// bytes from its row's start.  Vectors that hold bytes of several chunks, and
+// the row's ends, are read and where necessary stored element by element.
+// ES: bytes per element.
+// Measured on MI355X, step schedule -> walk: N=128 float32 1 MiB 7062 -> 2830
+// us, N=1000 float32 256 B 114 -> 57 us, 252 B 148 -> 52 us, N=24 bf16 64 KiB
+// 28 -> 21 us a call.
+template <int ES>
+__global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(GatherCtx cx) {
+  constexpr int kElems = 16 / ES;
+  using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
+  const uint32_t x8 = blockIdx.x % 8, j8 = blockIdx.x / 8;
+  const uint32_t blk = (j8 / cx.grain) * 8 * cx.grain + x8 * cx.grain + j8 % cx.grain;
+  if (blk >= cx.blocks) return;
+  const uint32_t g = blk / cx.tiles, tile = blk - g * cx.tiles;
+  // receivers r0, r0 + period, ...: `run` of them
+  const int turn = (int)g / cx.period, r0 = (int)g - turn * cx.period + turn * cx.run * cx.period;
+  if (r0 >= cx.N) return;
+  const int64_t C = cx.chunk_bytes;
+  const int64_t tile0 = (int64_t)tile * kGatherTile - (int64_t)((uintptr_t)cx.recv[r0] & 127);  // may be negative
+  if (tile0 >= cx.row_bytes) return;
+  const int64_t start = tile0 > 0 ? tile0 : 0;
+  const int x0 = cx.row_bytes < (int64_t(1) << 32) ? (int)((uint32_t)start / (uint32_t)C) : (int)(start / C);
+
+  const int off = (int)threadIdx.x * 16;
+  const int64_t o = tile0 + off;               // first byte in the row
+  const int64_t left = cx.row_bytes - o;
+  const int lo = o < 0 ? (o > -16 ? (int)-o : 16) : 0;  // bytes [lo, hi) are the row's
+  const int hi = left < 16 ? (int)left : 16;
+  const int64_t t = tile0 - x0 * C + off;      // first byte from chunk x0's start; negative before the row
+  const int q = C >= kGatherTile ? (t >= C ? 1 : 0) : t > 0 ? (int)((uint32_t)t / (uint32_t)C) : 0;
+  const int first = x0 + q;                    // chunks the vector holds bytes of
+  const int64_t at = t - q * C;                // its first byte in chunk `first`
+  const bool whole = lo == 0 && hi == 16;
+  int last = first;
+  v4u val = {};
+  if (whole && at + 16 <= C) {
+    val = ldg<v4u, false, ES>((const char*)cx.send[first] + at);
+  } else if (lo < hi) {
+    int64_t i = at;
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < kElems; ++e) {
+      if (e * ES >= lo && e * ES < hi) {
+        if (i >= C) i -= C, ++last;
+        const uint32_t b = ldg<elem_t, false>((const char*)cx.send[last] + i);
+        w[e * ES / 4] |= b << (e * ES % 4 * 8);
+      }
+      i += ES;
+    }
+    val = v4u{w[0], w[1], w[2], w[3]};
+  }
+  for (int k = 0, r = r0; k < cx.run && r < cx.N; ++k, r += cx.period) {
+    char* const row = (char*)cx.recv[r];
+    const bool inplace = (const char*)cx.send[r] == row + r * C;  // rank r's chunk is there already
+    char* const dst = row + tile0 + off;
+    if (whole && !(inplace && first <= r && r <= last)) {
+      stg<true, ES>(dst, val);
+    } else if (lo < hi) {
+      int x = first;
+      int64_t i = at;
+#pragma unroll
+      for (int e = 0; e < kElems; ++e) {
+        if (e * ES >= lo && e * ES < hi) {
+          if (i >= C) i -= C, ++x;
+          if (!(inplace && x == r)) stg<false>(dst + e * ES, (elem_t)(val[e * ES / 4] >> (e * ES % 4 * 8)));
+        }
+        i += ES;
+      }
+    }
+  }
+}
+
+// Receivers per workgroup: as many as make one round of workgroups
+// (kGatherBlocks, what the chip holds) out of a small operation, at most 4.
+// One receiver each costs a chain of dependent loads per vector (N=24 bf16 64
+// KiB: 1, 2, 3, 4, 6 receivers 15.2, 8.0, 7.9, 7.8, 8.1 us); more than 4 only
+// write more rows at once (N=300 float32 4 KiB: 4, 6, 8 receivers 56, 60, 60
+// us; N=1000 252 B: 39, 42, 44 us).  A tiny operation is best spread (N=13 bf16
+// 2002 B: 3.8, 4.1, 4.8 us at 1, 2, 4).
+constexpr int kGatherRun = 4;
+constexpr int64_t kGatherBlocks = 2048;
+
+hipError_t launch_walk_ag(GatherCtx cx, int64_t recv_stride, int esize, hipStream_t stream) {
+  // Rows a period apart start at the same offset from a line.  With too few
+  // rows for that to leave kGatherRun in a class, neighbours share a workgroup
+  // (N=37 float32 9999 elements, period 32: 13 us against 28 us apart).
+  cx.period = 1;
+  for (int64_t s = recv_stride % 128; s % 128; s += recv_stride % 128) ++cx.period;
+  if (cx.period * kGatherRun > cx.N) cx.period = 1;
+  // a tile more for rows that start up to 127 bytes past a line
+  const int64_t tiles = (cx.row_bytes + 127 + kGatherTile - 1) / kGatherTile;
+  cx.run = (int32_t)std::min<int64_t>(kGatherRun, (tiles * cx.N + kGatherBlocks - 1) / kGatherBlocks);
+  const int64_t turns = ((cx.N + cx.period - 1) / cx.period + cx.run - 1) / cx.run;
+  const int64_t blocks = tiles * turns * cx.period;
+  if (blocks > (int64_t(1) << 30)) return hipErrorInvalidValue;
+  cx.tiles = (uint32_t)tiles;
+  cx.blocks = (uint32_t)blocks;
+  // Order: tiles of the same receivers follow each other.  Runs of them per
+  // XCD for large operations only (N=128 float32 1 MiB, 1.05 M blocks: 2967 us
+  // one by one, 2880 us with runs of 256; N=300 4 KiB, 22500: 56 and 64 us).
+  cx.grain = blocks >= (1 << 18) ? 256 : 1;
+  const uint64_t pass = 8ull * cx.grain;
+  const dim3 grid((unsigned)((blocks + pass - 1) / pass * pass));
+  if (esize == 2)
+    hipLaunchKernelGGL(walk_ag_kernel<2>, grid, dim3(kGatherThreads), 0, stream, cx);
+  else
+    hipLaunchKernelGGL(walk_ag_kernel<4>, grid, dim3(kGatherThreads), 0, stream, cx);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 template <class T>
@@ -323,7 +464,16 @@ hipError_t launch_walk_rs(const WalkCtx& cx, bool streaming, hipStream_t stream)
   return streaming ? launch_walk_rs_t<T, true>(cx, stream) : launch_walk_rs_t<T, false>(cx, stream);
 }
 
-hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, hipStream_t stream) {
+hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, int64_t recv_stride, hipStream_t stream) {
+  if (v == kAgVec || v == kAgVecU || v == kAgS4 || v == kAgS2) {
+    GatherCtx gx{};
+    gx.send = cx.send;
+    gx.recv = cx.recv;
+    gx.chunk_bytes = cx.count * cx.esize;
+    gx.row_bytes = cx.N * gx.chunk_bytes;
+    gx.N = cx.N;
+    return launch_walk_ag(gx, recv_stride, (int)cx.esize, stream);
+  }
   const int64_t per = 16 / cx.esize;
   if (cx.count < kWalkLeastElems || cx.N > kWalkMostRanks) return hipErrorInvalidValue;
   WalkCtx wx{};

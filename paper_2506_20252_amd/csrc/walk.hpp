@@ -15,8 +15,11 @@ constexpr int kWalkMostRanks = 4096;
 // elements 66 / 56 us; N = 16 and 100, 16 elements: the walk 2-15% faster).
 constexpr int64_t kWalkLeastElems = 16;
 
-// The operation of variant v (reduce-scatter) over the buffers of cx.send and
-// cx.recv.  streaming: nontemporal accesses.
-hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, hipStream_t stream);
+// The operation of variant v over the buffers of cx.send and cx.recv.
+// streaming: nontemporal accesses (reduce-scatter).  recv_stride: the bytes
+// from one rank's receive buffer to the next one's, where that is the same for
+// all (all-gather: how its receivers share workgroups follows from it; any
+// value gives the same result).
+hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, int64_t recv_stride, hipStream_t stream);
 
 }  // namespace pat

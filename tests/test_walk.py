@@ -97,7 +97,7 @@ def test_walked_reducescatter(n, count, dtype, layout, entry):
     outs = []
     for fusion in ("auto", "off"):
         for r in recv:
-            r.view(torch.uint8).fill_(0xA5) if r.data_ptr() % 4 == 0 else r.fill_(1)
+            r.view(torch.uint8).fill_(0xA5)
         pat.check(pat.pat_set_top_fusion(fusion))
         try:
             pat.check(getattr(pat, "pat_" + entry)(S, R, count, dtype, pat.PAT_SUM, n, stream))
@@ -150,3 +150,43 @@ def test_walked_reducescatter_in_place_and_special_values(n, count, dtype):
         a[a.isnan()] = 0
         b[b.isnan()] = 0
     assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,count,dtype", [
+    (2, 1, "bfloat16"), (3, 1, "float32"), (5, 7, "bfloat16"), (9, 3, "int32"), (13, 1001, "bfloat16"),
+    (24, 4096, "bfloat16"), (37, 999, "float32"), (64, 1023, "bfloat16"), (130, 33, "float32"),
+    (300, 17, "bfloat16"), (300, 1024, "float32"), (1000, 63, "float32"), (1025, 2, "bfloat16"),
+])
+@pytest.mark.parametrize("layout", ["rows", "skewed", "separate", "inplace"])
+def test_walked_allgather(n, count, dtype, layout):
+    """Every receive row is the concatenation: chunks smaller and larger than
+    a vector and a tile, rows that start anywhere in a line, receivers that
+    share a workgroup side by side or a period apart; nothing outside the rows
+    changes."""
+    print(f"[gpu] walk allgather n={n} count={count} {dtype} {layout}", file=sys.stderr, flush=True)
+    dev = torch.device("cuda:0")
+    pat.check(pat.pat_set_exec_mode("stream"))
+    stream = torch.cuda.current_stream()
+    skew, gap = {"skewed": (3, 5), "inplace": (1, 1)}.get(layout, (0, 0))
+    whole = torch.empty(n * (n * count + gap) + skew, dtype=TORCH[dtype], device=dev).random_(0, 100)
+    recv = [whole[skew + r * (n * count + gap): skew + r * (n * count + gap) + n * count] for r in range(n)]
+    if layout == "separate":
+        recv = [torch.empty(n * count, dtype=TORCH[dtype], device=dev) for _ in range(n)]
+    send = rows(n, count, dtype, "rows" if layout == "inplace" else layout)
+    for x in range(n):
+        synth.fill(send[x], DIST[dtype], 77 + n, x)
+    want = torch.cat([s.clone() for s in send])
+    if layout == "inplace":
+        for x in range(n):
+            recv[x][x * count:(x + 1) * count] = send[x]
+        send = [recv[x][x * count:(x + 1) * count] for x in range(n)]
+    mark = torch.ones(whole.numel(), dtype=torch.bool, device=dev)
+    for r in range(n):
+        mark[skew + r * (n * count + gap): skew + r * (n * count + gap) + n * count] = False
+    outside = whole[mark].clone()
+    pat.check(pat.pat_allgather(pat.pointer_array(send), pat.pointer_array(recv), count, dtype, n, stream))
+    torch.cuda.synchronize()
+    bad = [r for r in range(n) if not torch.equal(recv[r].view(torch.uint8), want.view(torch.uint8))]
+    assert not bad, bad[:8]
+    assert torch.equal(whole[mark], outside)
