@@ -23,7 +23,7 @@
  *   - Status codes only; nothing is thrown across this boundary.
  *   - `sendbufs` / `recvbufs` are HOST arrays of `nranks` DEVICE pointers,
  *     read during the call only (the library copies them into a device
- *     table it owns).  The buffers themselves are owned by the caller and
+ *     table it owns, or passes them with the kernel launch).  The buffers themselves are owned by the caller and
  *     must stay valid until `stream` has finished the operation.
  *   - Calls are asynchronous with respect to the host and ordered on
  *     `stream`.  Calls that use the same (operation, nranks, count, dtype,

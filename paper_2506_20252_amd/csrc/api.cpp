@@ -237,17 +237,22 @@ struct Plan {
   int device = 0;
   pat::DevEntry* d_entries = nullptr;
   pat::DevStep* d_steps[3] = {nullptr, nullptr, nullptr};
-  const void** d_send = nullptr;
-  void** d_recv = nullptr;
+  const void** d_send = nullptr;  // 2N pointers: the send buffers', then the receive buffers'
+  void** d_recv = nullptr;        // d_send + N
   char* d_slots = nullptr;
   char* d_rootacc = nullptr;
   unsigned* d_sync = nullptr;  // persistent-kernel counters: [2] status, work queue from [4]
   size_t sync_words = 0;
   std::vector<const void*> h_send;
   std::vector<void*> h_recv;
-  void** pinned = nullptr;  // 2N pointers staged for upload
-  hipEvent_t upload_done = nullptr;
-  bool upload_pending = false;
+  // Staging for pointer-table uploads, kStages sets of 2N pointers taken in
+  // turn, so that a call with new buffers does not wait for the upload of the
+  // call before it (which waits for that call's predecessors on the stream).
+  static constexpr int kStages = 4;
+  void** pinned = nullptr;
+  hipEvent_t upload_done[kStages] = {};
+  bool upload_pending[kStages] = {};
+  int stage = 0;
   // Captured graphs by [vec][own_copy] and fused step range (s0, s1): a
   // change of the fusion setting selects or captures its own graph.
   std::map<std::tuple<int, int, int, int>, hipGraphExec_t> graphs;
@@ -276,12 +281,12 @@ struct Plan {
     for (auto& kv : graphs)
       if (kv.second) (void)hipGraphExecDestroy(kv.second);
     if (done) (void)hipEventDestroy(done);
-    if (upload_done) (void)hipEventDestroy(upload_done);
+    for (hipEvent_t e : upload_done)
+      if (e) (void)hipEventDestroy(e);
     if (pinned) (void)hipHostFree(pinned);
     (void)hipFree(d_entries);
     for (auto* p : d_steps) (void)hipFree(p);
-    (void)hipFree(d_send);
-    (void)hipFree(d_recv);
+    (void)hipFree(d_send);  // d_recv too
     (void)hipFree(d_slots);
     (void)hipFree(d_rootacc);
     (void)hipFree(d_sync);
@@ -472,8 +477,8 @@ pat_status_t create_plan(int coll, int N, int64_t count, pat_dtype_t dt, size_t 
   if ((s = alloc((void**)&p->d_entries, d.entries.size() * sizeof(pat::DevEntry))) != PAT_OK) return s;
   for (int v = 0; v < 3; ++v)
     if ((s = alloc((void**)&p->d_steps[v], h.steps[v].size() * sizeof(pat::DevStep))) != PAT_OK) return s;
-  if ((s = alloc((void**)&p->d_send, N * sizeof(void*))) != PAT_OK) return s;
-  if ((s = alloc((void**)&p->d_recv, N * sizeof(void*))) != PAT_OK) return s;
+  if ((s = alloc((void**)&p->d_send, 2 * N * sizeof(void*))) != PAT_OK) return s;
+  p->d_recv = (void**)(p->d_send + N);
   if ((s = alloc((void**)&p->d_slots, size_t(h.slot_rank_stride) * N)) != PAT_OK) return s;
   if ((s = alloc((void**)&p->d_rootacc, size_t(h.rootacc_stride) * N)) != PAT_OK) return s;
   p->sync_words = pat::queue_words(h.steps[0].size());  // every path has the same steps
@@ -492,8 +497,8 @@ pat_status_t create_plan(int coll, int N, int64_t count, pat_dtype_t dt, size_t 
     if (!h.steps[v].empty())
       HIP_TRY(hipMemcpy(p->d_steps[v], h.steps[v].data(), h.steps[v].size() * sizeof(pat::DevStep),
                         hipMemcpyHostToDevice));
-  HIP_TRY(hipHostMalloc((void**)&p->pinned, 2 * size_t(N) * sizeof(void*), hipHostMallocDefault));
-  HIP_TRY(hipEventCreateWithFlags(&p->upload_done, hipEventDisableTiming));
+  HIP_TRY(hipHostMalloc((void**)&p->pinned, Plan::kStages * 2 * size_t(N) * sizeof(void*), hipHostMallocDefault));
+  for (hipEvent_t& e : p->upload_done) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   HIP_TRY(hipEventCreateWithFlags(&p->done, hipEventDisableTiming));
   if (const char* e = std::getenv("PAT_STEP_CLOCK")) p->step_clock = e[0] == '1';
   if (const char* e = std::getenv("PAT_DEBUG")) {
@@ -509,6 +514,27 @@ pat_status_t create_plan(int coll, int N, int64_t count, pat_dtype_t dt, size_t 
   *out = p.get();
   g_plans[PlanKey(coll, N, count, (int)dt, budget, order, device, agg)] = std::move(p);
   return PAT_OK;
+}
+
+// The common layouts of overlaps_ok in O(N): receive buffers in ascending
+// order, none reaching into the next, and either every send buffer outside
+// their span, or every rank in place with the larger of its two buffers (the
+// one that holds the other) clear of its neighbours' too.  False: not one of
+// these.
+bool overlaps_ok_fast(int coll, const void* const* send, void* const* recv, int N, size_t send_bytes,
+                      size_t recv_bytes, size_t chunk_bytes) {
+  const uintptr_t lo = (uintptr_t)recv[0], hi = (uintptr_t)recv[N - 1] + recv_bytes;
+  bool apart = true, outside = true, inplace = true, sends_apart = true;
+  for (int r = 0; r < N; ++r) {
+    const uintptr_t s = (uintptr_t)send[r], q = (uintptr_t)recv[r];
+    outside &= s >= hi || s + send_bytes <= lo;
+    inplace &= coll == 0 ? s == q + uintptr_t(r) * chunk_bytes : q == s + uintptr_t(r) * chunk_bytes;
+    if (r + 1 < N) {
+      apart &= (uintptr_t)recv[r + 1] >= q + recv_bytes;
+      sends_apart &= (uintptr_t)send[r + 1] >= s + send_bytes;
+    }
+  }
+  return apart && (outside || (inplace && sends_apart));
 }
 
 // Receive buffers may not overlap anything except the in-place alias of the
@@ -542,15 +568,14 @@ bool overlaps_ok(int coll, const void* const* send, void* const* recv, int N, si
   return true;
 }
 
-// The pointer set a thread last passed the per-pointer checks with, and what
-// they found.  A caller that reuses its buffers passes the same set call after
-// call; comparing it costs O(N) instead of the checks' O(N log N).
+// The pointer set a thread last passed the general overlap check with.  A
+// caller that reuses its buffers passes the same set call after call;
+// comparing it costs O(N) instead of the check's O(N log N).
 struct CheckedPointers {
   int coll = -1, N = 0, dt = -1;
   size_t count = 0;
   std::vector<const void*> send;
   std::vector<void*> recv;
-  bool vec = false;
 };
 thread_local CheckedPointers t_checked;
 
@@ -626,32 +651,30 @@ pat_status_t check_args(int coll, const void* const* send, void* const* recv, si
     return PAT_OK;
   }
   const size_t chunk = count * es;
+  const size_t send_bytes = coll == 0 ? chunk : chunk * N;
+  const size_t recv_bytes = coll == 0 ? chunk * N : chunk;
+  uintptr_t bits = 0;
+  bool null = false;
+  for (int r = 0; r < N; ++r) {
+    null |= !send[r] | !recv[r];
+    bits |= (uintptr_t)send[r] | (uintptr_t)recv[r];
+  }
+  if (null || bits % es) return PAT_ERR_INVALID_ARGUMENT;
+  *vec = bits % 16 == 0;
+  if (overlaps_ok_fast(coll, send, recv, N, send_bytes, recv_bytes, chunk)) return PAT_OK;
   CheckedPointers& ck = t_checked;
   const bool checked = ck.coll == coll && ck.N == N && ck.dt == (int)dt && ck.count == count &&
                        !std::memcmp(ck.send.data(), send, N * sizeof(void*)) &&
                        !std::memcmp(ck.recv.data(), recv, N * sizeof(void*));
-  if (checked) {
-    *vec = ck.vec;
-    return PAT_OK;
-  }
+  if (checked) return PAT_OK;
   ck.coll = -1;  // invalid until this set passes
-  bool v = true;
-  for (int r = 0; r < N; ++r) {
-    if (!send[r] || !recv[r]) return PAT_ERR_INVALID_ARGUMENT;
-    if (((uintptr_t)send[r] | (uintptr_t)recv[r]) % es) return PAT_ERR_INVALID_ARGUMENT;
-    if (((uintptr_t)send[r] | (uintptr_t)recv[r]) % 16) v = false;
-  }
-  const size_t send_bytes = coll == 0 ? chunk : chunk * N;
-  const size_t recv_bytes = coll == 0 ? chunk * N : chunk;
   if (!overlaps_ok(coll, send, recv, N, send_bytes, recv_bytes, chunk)) return PAT_ERR_INVALID_ARGUMENT;
   ck.send.assign(send, send + N);
   ck.recv.assign(recv, recv + N);
   ck.N = N;
   ck.dt = (int)dt;
   ck.count = count;
-  ck.vec = v;
   ck.coll = coll;
-  *vec = v;
   return PAT_OK;
 }
 
@@ -794,13 +817,12 @@ bool walk_applies(const HostPlan& h) {
   return !d.pipelined && fusion_now() == PAT_FUSION_AUTO && !step_schedule_asked();
 }
 
-hipError_t enqueue_walk(const HostPlan& h, pat_dtype_t dt, int vi, const pat::KCtx& cx, void* const* recv,
+hipError_t enqueue_walk(const HostPlan& h, pat_dtype_t dt, int vi, const pat::KCtx& cx, const pat::WalkRows& rows,
                         hipStream_t q) {
   const pat::PlanDesc& d = h.desc;
   const double input = double(d.N) * d.N * double(d.count) * d.esize_in;
   pat::TreeRange tr{};
-  tr.walk = 1;
-  tr.walk_recv_stride = (int64_t)((uintptr_t)recv[1] - (uintptr_t)recv[0]);
+  tr.walk = &rows;
   return pat::launch_tree(variant_for(d.coll, dt, vi), input >= kWalkStreamingBytes, cx, tr, q);
 }
 
@@ -907,21 +929,30 @@ pat_status_t run(int coll, const void* const* send, void* const* recv, size_t co
   const int vi = path_for(h, vec);
   const bool own_copy = needs_own_copy(coll, send, recv, N, chunk);
 
+  const int mode = mode_now();
+  const pat::WalkRows rows = pat::walk_rows(send, recv, N);
+  const bool walk = mode == PAT_EXEC_STREAM && !g_trace.armed && !plan->step_clock && walk_applies(h);
+  // A walk whose launch carries the buffers' addresses uses nothing of the
+  // plan's device memory.
+  const bool on_device = !walk || rows.table;
+
   // Pointer tables: upload only when they changed since the last call.  The
   // remembered set is replaced only once its upload is queued.
   const bool same = plan->h_send.size() == size_t(N) &&
                     !std::memcmp(plan->h_send.data(), send, N * sizeof(void*)) &&
                     !std::memcmp(plan->h_recv.data(), recv, N * sizeof(void*));
-  if (!same) {
-    if (plan->upload_pending) HIP_TRY(hipEventSynchronize(plan->upload_done));
+  if (on_device && !same) {
+    const int k = plan->stage;
+    if (plan->upload_pending[k]) HIP_TRY(hipEventSynchronize(plan->upload_done[k]));
     plan->h_send.clear();
     plan->h_recv.clear();
-    std::memcpy(plan->pinned, send, N * sizeof(void*));
-    std::memcpy(plan->pinned + N, recv, N * sizeof(void*));
-    HIP_TRY(hipMemcpyAsync(plan->d_send, plan->pinned, N * sizeof(void*), hipMemcpyHostToDevice, stream));
-    HIP_TRY(hipMemcpyAsync(plan->d_recv, plan->pinned + N, N * sizeof(void*), hipMemcpyHostToDevice, stream));
-    HIP_TRY(hipEventRecord(plan->upload_done, stream));
-    plan->upload_pending = true;
+    void** const staged = plan->pinned + size_t(k) * 2 * N;
+    std::memcpy(staged, send, N * sizeof(void*));
+    std::memcpy(staged + N, recv, N * sizeof(void*));
+    HIP_TRY(hipMemcpyAsync(plan->d_send, staged, 2 * N * sizeof(void*), hipMemcpyHostToDevice, stream));
+    HIP_TRY(hipEventRecord(plan->upload_done[k], stream));
+    plan->upload_pending[k] = true;
+    plan->stage = (k + 1) % Plan::kStages;
     plan->h_send.assign(send, send + N);
     plan->h_recv.assign(recv, recv + N);
   }
@@ -941,8 +972,9 @@ pat_status_t run(int coll, const void* const* send, void* const* recv, size_t co
 
   const pat::Variant var = variant_for(coll, dt, vi);
   const auto& steps = h.steps[vi];
-  const int mode = mode_now();
-  if (mode == PAT_EXEC_DATAFLOW) {
+  if (walk) {
+    HIP_TRY(enqueue_walk(h, dt, vi, cx, rows, stream));
+  } else if (mode == PAT_EXEC_DATAFLOW) {
     // The relaxed bf16 reduce-scatter gives partial vectors work items of
     // their own, spanning many edges: dataflow runs its element-wide twin.
     const int dvi = pat::variant_partial_items(var) ? 0 : vi;
@@ -989,8 +1021,6 @@ pat_status_t run(int coll, const void* const* send, void* const* recv, size_t co
         std::fprintf(stderr, "[pat] persistent launch: capacity=%d cus=%d grid=%d steps=%d\n",
                      capacity, plan->cus, grid, cx.nsteps);
     HIP_TRY(pat::launch_persistent(var, nt, cx, grid, stream));
-  } else if (mode == PAT_EXEC_STREAM && !g_trace.armed && !plan->step_clock && walk_applies(h)) {
-    HIP_TRY(enqueue_walk(h, dt, vi, cx, recv, stream));
   } else {
     const pat::TreeRange tr = tree_range(h, vi);
     if (mode == PAT_EXEC_STREAM && plan->step_clock && tr.s1 > tr.s0) {
@@ -1032,8 +1062,10 @@ pat_status_t run(int coll, const void* const* send, void* const* recv, size_t co
       HIP_TRY(hipGraphLaunch(exec, stream));
     }
   }
-  HIP_TRY(hipEventRecord(plan->done, stream));
-  plan->used = true;
+  if (on_device) {
+    HIP_TRY(hipEventRecord(plan->done, stream));
+    plan->used = true;
+  }
   plan->last_use = ++g_tick;
   return PAT_OK;
 }
@@ -1117,7 +1149,8 @@ pat_status_t run_noalloc(int coll, const void* const* send, void* const* recv, s
   const HostPlan& h = ss.plan;
   const int vi = path_for(h, vec);
   const bool walk = walk_applies(h);
-  if (!walk && ss.vi != vi) {  // a walk reads the pointer tables only
+  const pat::WalkRows rows = pat::walk_rows(send, recv, N);
+  if (!walk && ss.vi != vi) {  // a walk reads the pointer tables at most
     ss.vi = -1;
     const auto& entries = h.desc.entries;
     if (!entries.empty())
@@ -1129,7 +1162,7 @@ pat_status_t run_noalloc(int coll, const void* const* send, void* const* recv, s
   }
   const bool same = ss.send.size() == size_t(N) && !std::memcmp(ss.send.data(), send, N * sizeof(void*)) &&
                     !std::memcmp(ss.recv.data(), recv, N * sizeof(void*));
-  if (!same) {
+  if ((!walk || rows.table) && !same) {
     ss.send.assign(send, send + N);
     ss.recv.assign(recv, recv + N);
     HIP_TRY(hipMemcpyAsync(base + ss.off_send, ss.send.data(), N * sizeof(void*), hipMemcpyHostToDevice, stream));
@@ -1140,7 +1173,8 @@ pat_status_t run_noalloc(int coll, const void* const* send, void* const* recv, s
                                 (const pat::DevEntry*)(base + ss.off_entries),
                                 (const pat::DevStep*)(base + ss.off_steps), count, N,
                                 needs_own_copy(coll, send, recv, N, chunk));
-  HIP_TRY(walk ? enqueue_walk(h, dt, vi, cx, recv, stream) : enqueue_stream(h, coll, dt, vi, cx, tree_range(h, vi), stream));
+  HIP_TRY(walk ? enqueue_walk(h, dt, vi, cx, rows, stream)
+               : enqueue_stream(h, coll, dt, vi, cx, tree_range(h, vi), stream));
   return PAT_OK;
 }
 

@@ -111,10 +111,9 @@ struct TreeRange {
   int32_t c0, c1;
   int32_t cn, ce0;
   int16_t cend[kTreeCacheSteps];
-  // 1: the whole operation as one walk launch (walk.hpp), which reads only
-  // the context's pointer tables and sizes; the fields above are unused.
-  int32_t walk;
-  int64_t walk_recv_stride;  // bytes between the ranks' receive buffers (see launch_walk)
+  // Not null: the whole operation as one walk launch over these buffers
+  // (walk.hpp); the fields above are unused.  Host memory.
+  const struct WalkRows* walk;
 };
 hipError_t launch_tree(Variant v, bool streaming, const KCtx& cx, const TreeRange& tr, hipStream_t stream);
 // Persistent execution: one launch of `grid` workgroups that take per-step

@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
+#include <cstring>
 #include <type_traits>
 
 #include "device_access.hpp"
@@ -28,9 +30,74 @@
 namespace pat {
 namespace {
 
+// How a kernel finds rank r's buffers: at base + r * stride (SPACED kernels),
+// else in a pointer table, which is in device memory or comes with the launch
+// (RowPointers, read from the kernel-argument segment).
+struct RowsArg {
+  uint64_t send0, recv0;
+  int64_t send_stride, recv_stride;
+  uint64_t send_table, recv_table;  // 0: RowPointers
+};
+struct RowPointers {
+  uint64_t send[kWalkInlineRanks], recv[kWalkInlineRanks];
+};
+
+// Pointer tables do not change during a launch: constant memory, which scalar
+// loads serve where the rank is uniform.
+#define PAT_CONSTANT __attribute__((address_space(4)))
+typedef const PAT_CONSTANT uint64_t* RowTable;
+
+// A kernel's one argument: the pointers' place in the argument segment is
+// then known.
+template <class Ctx, bool SPACED>
+struct WalkArgs {
+  Ctx cx;
+};
+template <class Ctx>
+struct WalkArgs<Ctx, false> {
+  Ctx cx;
+  RowPointers ptrs;
+};
+
+template <class Ctx>
+__device__ __forceinline__ RowTable row_table(uint64_t table, size_t member) {
+  using IndexedArgs = WalkArgs<Ctx, false>;
+  if (table) return (RowTable)table;
+  return (RowTable)((const PAT_CONSTANT char*)__builtin_amdgcn_kernarg_segment_ptr() +
+                    offsetof(IndexedArgs, ptrs) + member);
+}
+template <bool SPACED, class Ctx>
+__device__ __forceinline__ const char* send_row(const Ctx& cx, int r) {
+  if constexpr (SPACED) return (const char*)(cx.rows.send0 + (uint64_t)(r * cx.rows.send_stride));
+  return (const char*)row_table<Ctx>(cx.rows.send_table, offsetof(RowPointers, send))[r];
+}
+template <bool SPACED, class Ctx>
+__device__ __forceinline__ char* recv_row(const Ctx& cx, int r) {
+  if constexpr (SPACED) return (char*)(cx.rows.recv0 + (uint64_t)(r * cx.rows.recv_stride));
+  return (char*)row_table<Ctx>(cx.rows.recv_table, offsetof(RowPointers, recv))[r];
+}
+
+template <class Ctx, bool SPACED>
+void launch_kernel(void (*kernel)(WalkArgs<Ctx, SPACED>), dim3 grid, int threads, const Ctx& cx, const WalkRows& rows,
+                   hipStream_t stream) {
+  WalkArgs<Ctx, SPACED> a;
+  a.cx = cx;
+  if constexpr (!SPACED) {
+    if (!rows.table) {
+      std::memcpy(a.ptrs.send, rows.send, cx.N * sizeof(void*));
+      std::memcpy(a.ptrs.recv, rows.recv, cx.N * sizeof(void*));
+    }
+  }
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, a);
+}
+
+// What a kernel's context says about `rows` (device tables: kx's).
+RowsArg rows_arg(const KCtx& kx, const WalkRows& rows) {
+  return RowsArg{(uint64_t)rows.send[0], (uint64_t)rows.recv[0], rows.send_stride, rows.recv_stride,
+                 rows.table ? (uint64_t)kx.send : 0, rows.table ? (uint64_t)kx.recv : 0};
+}
 struct WalkCtx {
-  const void* const* send;  // [N] device pointers (device table)
-  void* const* recv;        // [N]
+  RowsArg rows;
   int64_t chunk_bytes;      // of a user chunk
   int64_t V;                // 16-byte vectors per chunk, a partial last one among them
   int32_t N;
@@ -153,8 +220,9 @@ __device__ __forceinline__ typename T::acc_t group_sum(const typename T::in_t (&
 // adds.  The bound is HBM's read rate.  Measured on MI355X, step schedule ->
 // walk: N=64 float32 1 MiB 1992 -> 654 us, N=128 bf16 4 MiB 52.6 -> 11.7 ms
 // (6.7 and 5.9 TB/s of input), N=1000 float32 256 B 139 -> 76 us a call.
-template <class T, int G, int MAXT, int LV, bool SPLIT, bool UNI, bool NT>
-__global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkCtx cx) {
+template <class T, int G, int MAXT, int LV, bool SPLIT, bool UNI, bool SPACED, bool NT>
+__global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkArgs<WalkCtx, SPACED> args) {
+  const WalkCtx& cx = args.cx;
   using in_t = typename T::in_t;
   using acc_t = typename T::acc_t;
   const int N = cx.N;
@@ -196,11 +264,17 @@ __global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkCtx cx) {
   const int p0 = SPLIT ? s * cx.w : 0;
   const int n = SPLIT && N - p0 > cx.w ? cx.w : N - p0;  // positions of this lane group
   if (live && n > 0) {
+    // The send buffer of position q (rank R + q, mod N).
+    const char* const row0 = SPACED ? send_row<SPACED>(cx, R) : nullptr;
+    auto row = [&](int q) -> const char* {
+      if constexpr (SPACED) return row0 + (R >= N - q ? (q - N) * cx.rows.send_stride : q * cx.rows.send_stride);
+      return send_row<SPACED>(cx, wrap_add(R, q, N));
+    };
     auto load = [&](in_t(&x)[G], int q, int m) {
       const char* p[G];
 #pragma unroll
       for (int j = 0; j < G; ++j)
-        if (j < m) p[j] = (const char*)cx.send[wrap_add(R, p0 + q + j, N)];
+        if (j < m) p[j] = row(p0 + q + j);
 #pragma unroll
       for (int j = 0; j < G; ++j)
         if (j < m) x[j] = ldg<in_t, NT, T::kElem>(p[j] + soff);
@@ -235,26 +309,29 @@ __global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkCtx cx) {
     if (!live) return;
   }
   const in_t out = T::narrow(sum);
-  char* const dst = (char*)cx.recv[R] + voff;
+  char* const dst = recv_row<SPACED>(cx, R) + voff;
   if (part)
     stg_from<NT, T::kElem>(dst, out, cx.back);
   else
     stg<NT, T::kElem>(dst, out);
 }
 
-// Grid of `blocks` workgroups in XCD runs of cx.grain.
-dim3 walk_grid(const WalkCtx& cx) {
-  const uint64_t run = 8ull * cx.grain;
-  return dim3((unsigned)((cx.blocks + run - 1) / run * run));
+// Grid of `blocks` workgroups in XCD runs of `grain`.
+dim3 walk_grid(uint64_t blocks, uint64_t grain) {
+  return dim3((unsigned)((blocks + 8 * grain - 1) / (8 * grain) * (8 * grain)));
 }
 
 template <class T, int G, int MAXT, int LV, bool SPLIT, bool NT>
-void launch_walk_rs_k(const WalkCtx& cx, bool uni, int threads, hipStream_t stream) {
-  if (uni)
-    hipLaunchKernelGGL((walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, NT>), walk_grid(cx), dim3(threads), 0, stream, cx);
+void launch_walk_rs_k(const WalkCtx& cx, const WalkRows& rows, bool uni, int threads, hipStream_t stream) {
+  const dim3 grid = walk_grid(cx.blocks, cx.grain);
+  if (rows.spaced && uni)
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, true, NT>, grid, threads, cx, rows, stream);
+  else if (rows.spaced)
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, true, NT>, grid, threads, cx, rows, stream);
+  else if (uni)
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, false, NT>, grid, threads, cx, rows, stream);
   else
-    hipLaunchKernelGGL((walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, NT>), walk_grid(cx), dim3(threads), 0, stream,
-                       cx);
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, false, NT>, grid, threads, cx, rows, stream);
 }
 
 // Slots of a lane group: the sub-tree it walks spans at most 2^(slots - 1)
@@ -291,7 +368,7 @@ constexpr int kWalkSpan = 8;
 constexpr int kWalkMostGroups = 16;
 
 template <class T, bool NT>
-hipError_t launch_walk_rs_t(WalkCtx cx, hipStream_t stream) {
+hipError_t launch_walk_rs_t(WalkCtx cx, const WalkRows& rows, hipStream_t stream) {
   int span = 1;
   while (span < cx.N) span *= 2;
   const int64_t waves = (cx.N * cx.V + 63) / 64;
@@ -311,11 +388,11 @@ hipError_t launch_walk_rs_t(WalkCtx cx, hipStream_t stream) {
   cx.blocks = (uint32_t)blocks;
   cx.grain = blocks >= 16384 ? 64 : 4;
   if (S == 1)
-    launch_walk_rs_k<T, walk_group<T>(1), 256, walk_slots<T>(1), false, NT>(cx, uni, threads, stream);
+    launch_walk_rs_k<T, walk_group<T>(1), 256, walk_slots<T>(1), false, NT>(cx, rows, uni, threads, stream);
   else if (S <= 4)
-    launch_walk_rs_k<T, walk_group<T>(4), 256, walk_slots<T>(4), true, NT>(cx, uni, threads, stream);
+    launch_walk_rs_k<T, walk_group<T>(4), 256, walk_slots<T>(4), true, NT>(cx, rows, uni, threads, stream);
   else
-    launch_walk_rs_k<T, walk_group<T>(16), 1024, walk_slots<T>(16), true, NT>(cx, uni, threads, stream);
+    launch_walk_rs_k<T, walk_group<T>(16), 1024, walk_slots<T>(16), true, NT>(cx, rows, uni, threads, stream);
   return hipGetLastError();
 }
 
@@ -328,8 +405,7 @@ hipError_t launch_walk_rs_t(WalkCtx cx, hipStream_t stream) {
 // 16-byte vectors of the concatenation (a tile) and a few receivers, reads the
 // tile once, into registers, and stores it to each receiver in turn.
 struct GatherCtx {
-  const void* const* send;  // [N] device pointers (device table)
-  void* const* recv;        // [N]
+  RowsArg rows;
   int64_t chunk_bytes;
   int64_t row_bytes;        // N * chunk_bytes
   int32_t N;
@@ -353,8 +429,9 @@ constexpr int kGatherTile = kGatherThreads * 16;  // bytes
 // Measured on MI355X, step schedule -> walk: N=128 float32 1 MiB 7062 -> 2830
 // us, N=1000 float32 256 B 114 -> 57 us, 252 B 148 -> 52 us, N=24 bf16 64 KiB
 // 28 -> 21 us a call.
-template <int ES>
-__global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(GatherCtx cx) {
+template <int ES, bool SPACED>
+__global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(WalkArgs<GatherCtx, SPACED> args) {
+  const GatherCtx& cx = args.cx;
   constexpr int kElems = 16 / ES;
   using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
   const uint32_t x8 = blockIdx.x % 8, j8 = blockIdx.x / 8;
@@ -365,7 +442,7 @@ __global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(GatherCtx cx) {
   const int turn = (int)g / cx.period, r0 = (int)g - turn * cx.period + turn * cx.run * cx.period;
   if (r0 >= cx.N) return;
   const int64_t C = cx.chunk_bytes;
-  const int64_t tile0 = (int64_t)tile * kGatherTile - (int64_t)((uintptr_t)cx.recv[r0] & 127);  // may be negative
+  const int64_t tile0 = (int64_t)tile * kGatherTile - (int64_t)((uintptr_t)recv_row<SPACED>(cx, r0) & 127);  // may be negative
   if (tile0 >= cx.row_bytes) return;
   const int64_t start = tile0 > 0 ? tile0 : 0;
   const int x0 = cx.row_bytes < (int64_t(1) << 32) ? (int)((uint32_t)start / (uint32_t)C) : (int)(start / C);
@@ -383,7 +460,7 @@ __global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(GatherCtx cx) {
   int last = first;
   v4u val = {};
   if (whole && at + 16 <= C) {
-    val = ldg<v4u, false, ES>((const char*)cx.send[first] + at);
+    val = ldg<v4u, false, ES>(send_row<SPACED>(cx, first) + at);
   } else if (lo < hi) {
     int64_t i = at;
     uint32_t w[4] = {0, 0, 0, 0};
@@ -391,7 +468,7 @@ __global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(GatherCtx cx) {
     for (int e = 0; e < kElems; ++e) {
       if (e * ES >= lo && e * ES < hi) {
         if (i >= C) i -= C, ++last;
-        const uint32_t b = ldg<elem_t, false>((const char*)cx.send[last] + i);
+        const uint32_t b = ldg<elem_t, false>(send_row<SPACED>(cx, last) + i);
         w[e * ES / 4] |= b << (e * ES % 4 * 8);
       }
       i += ES;
@@ -399,8 +476,8 @@ __global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(GatherCtx cx) {
     val = v4u{w[0], w[1], w[2], w[3]};
   }
   for (int k = 0, r = r0; k < cx.run && r < cx.N; ++k, r += cx.period) {
-    char* const row = (char*)cx.recv[r];
-    const bool inplace = (const char*)cx.send[r] == row + r * C;  // rank r's chunk is there already
+    char* const row = recv_row<SPACED>(cx, r);
+    const bool inplace = send_row<SPACED>(cx, r) == row + r * C;  // rank r's chunk is there already
     char* const dst = row + tile0 + off;
     if (whole && !(inplace && first <= r && r <= last)) {
       stg<true, ES>(dst, val);
@@ -429,7 +506,8 @@ __global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(GatherCtx cx) {
 constexpr int kGatherRun = 4;
 constexpr int64_t kGatherBlocks = 2048;
 
-hipError_t launch_walk_ag(GatherCtx cx, int64_t recv_stride, int esize, hipStream_t stream) {
+hipError_t launch_walk_ag(GatherCtx cx, const WalkRows& rows, int esize, hipStream_t stream) {
+  const int64_t recv_stride = rows.recv_stride;
   // Rows a period apart start at the same offset from a line.  With too few
   // rows for that to leave kGatherRun in a class, neighbours share a workgroup
   // (N=37 float32 9999 elements, period 32: 13 us against 28 us apart).
@@ -448,37 +526,36 @@ hipError_t launch_walk_ag(GatherCtx cx, int64_t recv_stride, int esize, hipStrea
   // XCD for large operations only (N=128 float32 1 MiB, 1.05 M blocks: 2967 us
   // one by one, 2880 us with runs of 256; N=300 4 KiB, 22500: 56 and 64 us).
   cx.grain = blocks >= (1 << 18) ? 256 : 1;
-  const uint64_t pass = 8ull * cx.grain;
-  const dim3 grid((unsigned)((blocks + pass - 1) / pass * pass));
-  if (esize == 2)
-    hipLaunchKernelGGL(walk_ag_kernel<2>, grid, dim3(kGatherThreads), 0, stream, cx);
+  const dim3 grid = walk_grid(cx.blocks, cx.grain);
+  if (rows.spaced)
+    launch_kernel(esize == 2 ? walk_ag_kernel<2, true> : walk_ag_kernel<4, true>, grid, kGatherThreads, cx, rows, stream);
   else
-    hipLaunchKernelGGL(walk_ag_kernel<4>, grid, dim3(kGatherThreads), 0, stream, cx);
+    launch_kernel(esize == 2 ? walk_ag_kernel<2, false> : walk_ag_kernel<4, false>, grid, kGatherThreads, cx, rows,
+                  stream);
   return hipGetLastError();
 }
 
 }  // namespace
 
 template <class T>
-hipError_t launch_walk_rs(const WalkCtx& cx, bool streaming, hipStream_t stream) {
-  return streaming ? launch_walk_rs_t<T, true>(cx, stream) : launch_walk_rs_t<T, false>(cx, stream);
+hipError_t launch_walk_rs(const WalkCtx& cx, const WalkRows& rows, bool streaming, hipStream_t stream) {
+  return streaming ? launch_walk_rs_t<T, true>(cx, rows, stream) : launch_walk_rs_t<T, false>(cx, rows, stream);
 }
 
-hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, int64_t recv_stride, hipStream_t stream) {
+hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, const WalkRows& rows, hipStream_t stream) {
+  if (!rows.spaced && !rows.table && cx.N > kWalkInlineRanks) return hipErrorInvalidValue;
   if (v == kAgVec || v == kAgVecU || v == kAgS4 || v == kAgS2) {
     GatherCtx gx{};
-    gx.send = cx.send;
-    gx.recv = cx.recv;
+    gx.rows = rows_arg(cx, rows);
     gx.chunk_bytes = cx.count * cx.esize;
     gx.row_bytes = cx.N * gx.chunk_bytes;
     gx.N = cx.N;
-    return launch_walk_ag(gx, recv_stride, (int)cx.esize, stream);
+    return launch_walk_ag(gx, rows, (int)cx.esize, stream);
   }
   const int64_t per = 16 / cx.esize;
   if (cx.count < kWalkLeastElems || cx.N > kWalkMostRanks) return hipErrorInvalidValue;
   WalkCtx wx{};
-  wx.send = cx.send;
-  wx.recv = cx.recv;
+  wx.rows = rows_arg(cx, rows);
   wx.N = cx.N;
   wx.chunk_bytes = cx.count * cx.esize;
   wx.V = (cx.count + per - 1) / per;
@@ -486,13 +563,13 @@ hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, int64_t recv_s
   switch (v) {  // whichever path the plan's pieces take: a walk has none
     case kRsI32S:
     case kRsI32Vec:
-    case kRsI32VecU: return launch_walk_rs<WI32>(wx, streaming, stream);
+    case kRsI32VecU: return launch_walk_rs<WI32>(wx, rows, streaming, stream);
     case kRsF32S:
     case kRsF32Vec:
-    case kRsF32VecU: return launch_walk_rs<WF32>(wx, streaming, stream);
+    case kRsF32VecU: return launch_walk_rs<WF32>(wx, rows, streaming, stream);
     case kRsB16S:
     case kRsB16Vec:
-    case kRsB16VecU: return launch_walk_rs<WB16>(wx, streaming, stream);
+    case kRsB16VecU: return launch_walk_rs<WB16>(wx, rows, streaming, stream);
     default: return hipErrorInvalidValue;
   }
 }

@@ -35,9 +35,13 @@ def bits(t):
 
 
 def rows(n, elems, dtype, layout):
-    """N rows of `elems` elements: rows of one tensor, rows one element off a
-    16-byte boundary with a gap between them, or N allocations."""
+    """N rows of `elems` elements: rows of one tensor, the same in descending
+    order or shuffled, rows one element off a 16-byte boundary with a gap
+    between them, or N allocations."""
     dev = torch.device("cuda:0")
+    if layout in ("reversed", "shuffled"):
+        r = rows(n, elems, dtype, "rows")[::-1]
+        return r if layout == "reversed" else [r[i] for i in np.random.default_rng(n).permutation(n)]
     if layout == "separate":
         return [torch.empty(elems, dtype=TORCH[dtype], device=dev) for _ in range(n)]
     skew, gap = (1, 3) if layout == "skewed" else (0, 0)
@@ -70,6 +74,58 @@ def test_walk_kernels_keep_their_slots_in_registers(walk_asm):
     assert not re.search(r"\bv_pk_(add|mul|fma)_f32\b", walk_asm)
 
 
+def test_overlap_checks_agree_with_the_definition():
+    """Which pointer sets are refused, whatever layout check answers: receive
+    buffers overlapping each other or another rank's send buffer, or their own
+    other than in place.  Without a GPU an accepted call ends at the first
+    device call (PAT_ERR_HIP), before any address is used."""
+    if torch.cuda.is_available():
+        pytest.skip("the addresses are made up: only where nothing can be launched")
+    rng = np.random.default_rng(11)
+    seen = set()
+    for trial in range(4000):
+        n, count, gather = int(rng.integers(2, 7)), int(rng.integers(1, 9)), bool(rng.integers(2))
+        chunk = 4 * count
+        sb, rb = (chunk, n * chunk) if gather else (n * chunk, chunk)
+        base = 0x10000
+        kind = int(rng.integers(4))
+        gap = 4 * int(rng.integers(0, 3))
+        big = max(sb, rb) + gap
+        if kind == 0:  # rows side by side
+            send = [base + r * (sb + gap) for r in range(n)]
+            recv = [base + n * (sb + gap) + r * (rb + gap) for r in range(n)]
+        elif kind == 1:  # in place
+            outer = [base + r * big for r in range(n)]
+            inner = [o + r * chunk for r, o in enumerate(outer)]
+            send, recv = (inner, outer) if gather else (outer, inner)
+        elif kind == 2:  # interleaved
+            send = [base + r * (sb + rb + gap) for r in range(n)]
+            recv = [s + sb for s in send]
+        else:
+            send = [base + 4 * int(rng.integers(0, 40 * n)) for _ in range(n)]
+            recv = [base + 4 * int(rng.integers(0, 40 * n)) for _ in range(n)]
+        if rng.integers(2):  # one pointer moved, or two swapped
+            side = send if rng.integers(2) else recv
+            i, j = (int(x) for x in rng.integers(0, n, 2))
+            if rng.integers(2):
+                side[i] += 4 * int(rng.integers(-3, 4))
+            else:
+                side[i], side[j] = side[j], side[i]
+        ok = all(abs(recv[a] - recv[b]) >= rb for a in range(n) for b in range(a))
+        for a in range(n):
+            for b in range(n):
+                if send[a] < recv[b] + rb and recv[b] < send[a] + sb:
+                    alias = send[a] == recv[b] + b * chunk if gather else recv[b] == send[a] + a * chunk
+                    ok = ok and a == b and alias
+        if gather:
+            st = pat.pat_allgather(send, recv, count, "float32", n, None)
+        else:
+            st = pat.pat_reducescatter(send, recv, count, "float32", pat.PAT_SUM, n, None)
+        assert st == (pat.PAT_ERR_HIP if ok else pat.PAT_ERR_INVALID_ARGUMENT), (trial, kind, gather, send, recv)
+        seen.add((kind, ok))
+    assert seen >= {(0, True), (0, False), (1, True), (1, False), (2, True), (3, False)}
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,count,dtype,layout", [
     (2, 16, "float32", "rows"), (3, 17, "bfloat16", "skewed"), (5, 1000, "int32", "separate"),
@@ -79,7 +135,8 @@ def test_walk_kernels_keep_their_slots_in_registers(walk_asm):
     (200, 520, "float32", "rows"), (257, 250, "bfloat16", "rows"), (300, 75, "float32", "skewed"),
     (513, 67, "float32", "rows"), (1000, 64, "float32", "rows"), (1025, 33, "bfloat16", "rows"),
     (2049, 16, "float32", "rows"), (4096, 18, "bfloat16", "rows"), (4097, 16, "bfloat16", "rows"),
-    (31, 15, "float32", "rows"),
+    (31, 15, "float32", "rows"), (20, 1000, "bfloat16", "reversed"), (64, 333, "float32", "shuffled"),
+    (65, 40, "int32", "shuffled"), (300, 64, "float32", "reversed"), (600, 24, "bfloat16", "shuffled"),
 ])
 @pytest.mark.parametrize("entry", ["reducescatter", "reducescatter_noalloc"])
 def test_walked_reducescatter(n, count, dtype, layout, entry):
@@ -158,7 +215,7 @@ def test_walked_reducescatter_in_place_and_special_values(n, count, dtype):
     (24, 4096, "bfloat16"), (37, 999, "float32"), (64, 1023, "bfloat16"), (130, 33, "float32"),
     (300, 17, "bfloat16"), (300, 1024, "float32"), (1000, 63, "float32"), (1025, 2, "bfloat16"),
 ])
-@pytest.mark.parametrize("layout", ["rows", "skewed", "separate", "inplace"])
+@pytest.mark.parametrize("layout", ["rows", "skewed", "separate", "inplace", "reversed", "shuffled"])
 def test_walked_allgather(n, count, dtype, layout):
     """Every receive row is the concatenation: chunks smaller and larger than
     a vector and a tile, rows that start anywhere in a line, receivers that
@@ -171,8 +228,8 @@ def test_walked_allgather(n, count, dtype, layout):
     skew, gap = {"skewed": (3, 5), "inplace": (1, 1)}.get(layout, (0, 0))
     whole = torch.empty(n * (n * count + gap) + skew, dtype=TORCH[dtype], device=dev).random_(0, 100)
     recv = [whole[skew + r * (n * count + gap): skew + r * (n * count + gap) + n * count] for r in range(n)]
-    if layout == "separate":
-        recv = [torch.empty(n * count, dtype=TORCH[dtype], device=dev) for _ in range(n)]
+    if layout in ("separate", "reversed", "shuffled"):
+        recv = rows(n, n * count, dtype, layout)
     send = rows(n, count, dtype, "rows" if layout == "inplace" else layout)
     for x in range(n):
         synth.fill(send[x], DIST[dtype], 77 + n, x)
