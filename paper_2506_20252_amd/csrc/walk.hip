@@ -6,7 +6,7 @@
 // three transfers of a chunk per edge, where each input has to be read only
 // once.  The far-first linear walk of one tree (section "The PAT algorithm")
 // needs one chunk of intermediate buffer per distance, ceil(log2 N) in all;
-// over one 16-byte vector of the chunk that is a few registers, so a lane can
+// over one 4-element vector of the chunk that is a few registers, so a lane can
 // walk its vector's whole tree by itself.
 //
 // Reduce-scatter: lane (R, v) owns vector v of destination chunk R.  It reads
@@ -99,7 +99,7 @@ RowsArg rows_arg(const KCtx& kx, const WalkRows& rows) {
 struct WalkCtx {
   RowsArg rows;
   int64_t chunk_bytes;      // of a user chunk
-  int64_t V;                // 16-byte vectors per chunk, a partial last one among them
+  int64_t V;                // 4-element vectors per chunk, a partial last one among them
   int32_t N;
   int32_t back;             // a partial last vector begins this many elements inside the one before (0: none)
   int32_t w;                // positions per lane group, a power of two
@@ -112,7 +112,7 @@ struct WalkCtx {
 // may be moved back to end where the chunk ends.
 struct WI32 {
   using in_t = v4u;
-  static constexpr int kElem = 4, kElems = 4;
+  static constexpr int kElem = 4;
   struct acc_t {
     v4u a;
   };
@@ -123,7 +123,7 @@ struct WI32 {
 
 struct WF32 {
   using in_t = v4f;
-  static constexpr int kElem = 4, kElems = 4;
+  static constexpr int kElem = 4;
   struct acc_t {
     v4f a;
   };
@@ -132,21 +132,23 @@ struct WF32 {
   __device__ static acc_t add(const acc_t& x, const acc_t& y) { return {x.a + y.a}; }
 };
 
+// 8-byte vectors: 4 float32 partials per slot, as for float32, leave 64 VGPRs
+// and 8 waves per SIMD, where 16-byte vectors take 108 and 4 (measured on
+// MI355X, 16-byte / 8-byte: N=128 4 MiB 12.3 / 11.0 ms, N=64 2 MiB 1568 / 1402
+// us, N=24 64 KiB 10.0 / 8.4 us).
 struct WB16 {
-  using in_t = v4u;  // 8 bf16, element 2j in the low half of word j
-  static constexpr int kElem = 2, kElems = 8;
+  using in_t = v2u;  // 4 bf16, element 2j in the low half of word j
+  static constexpr int kElem = 2;
   struct acc_t {
-    v4f a, b;
+    v4f a;
   };
   __device__ static acc_t widen(const in_t& x) {
-    return {v4f{bf16_lo(x.x), bf16_hi(x.x), bf16_lo(x.y), bf16_hi(x.y)},
-            v4f{bf16_lo(x.z), bf16_hi(x.z), bf16_lo(x.w), bf16_hi(x.w)}};
+    return {v4f{bf16_lo(x.x), bf16_hi(x.x), bf16_lo(x.y), bf16_hi(x.y)}};
   }
   __device__ static in_t narrow(const acc_t& x) {
-    return v4u{bf16_rne(x.a.x) | (bf16_rne(x.a.y) << 16), bf16_rne(x.a.z) | (bf16_rne(x.a.w) << 16),
-               bf16_rne(x.b.x) | (bf16_rne(x.b.y) << 16), bf16_rne(x.b.z) | (bf16_rne(x.b.w) << 16)};
+    return v2u{bf16_rne(x.a.x) | (bf16_rne(x.a.y) << 16), bf16_rne(x.a.z) | (bf16_rne(x.a.w) << 16)};
   }
-  __device__ static acc_t add(const acc_t& x, const acc_t& y) { return {x.a + y.a, x.b + y.b}; }
+  __device__ static acc_t add(const acc_t& x, const acc_t& y) { return {x.a + y.a}; }
 };
 
 // Partials of complete sub-trees, one per distance, like the schedule's slots:
@@ -218,8 +220,8 @@ __device__ __forceinline__ typename T::acc_t group_sum(const typename T::in_t (&
 //
 // A lane reads G positions at a time and has the next G on the way while it
 // adds.  The bound is HBM's read rate.  Measured on MI355X, step schedule ->
-// walk: N=64 float32 1 MiB 1992 -> 654 us, N=128 bf16 4 MiB 52.6 -> 11.7 ms
-// (6.7 and 5.9 TB/s of input), N=1000 float32 256 B 139 -> 76 us a call.
+// walk: N=64 float32 1 MiB 1992 -> 650 us, N=128 bf16 4 MiB 52.6 -> 10.8 ms
+// (6.6 and 6.4 TB/s of input), N=1000 float32 256 B 139 -> 42 us a call.
 template <class T, int G, int MAXT, int LV, bool SPLIT, bool UNI, bool SPACED, bool NT>
 __global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkArgs<WalkCtx, SPACED> args) {
   const WalkCtx& cx = args.cx;
@@ -257,7 +259,7 @@ __global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkArgs<WalkCtx, SPACED>
     }
   }
   const bool part = cx.back && v == cx.V - 1;
-  const int64_t voff = v * 16 - (part ? cx.back * T::kElem : 0);
+  const int64_t voff = v * (int64_t)sizeof(in_t) - (part ? cx.back * T::kElem : 0);
   const int64_t soff = (int64_t)R * cx.chunk_bytes + voff;
 
   acc_t sum;
@@ -338,32 +340,40 @@ void launch_walk_rs_k(const WalkCtx& cx, const WalkRows& rows, bool uni, int thr
 // groups of positions.
 template <class T>
 constexpr int walk_slots(int S) {
-  return S <= 4 ? 6 : T::kElem == 2 ? 7 : 8;
+  return S <= 4 ? 6 : 8;
 }
 // Positions read at a time.  A whole tree: 4.  A part of one: float32 and
-// int32 2 (56 VGPRs with a chunk's own workgroups, 8 waves per SIMD), bf16 4.
+// int32 2 (56 VGPRs with a chunk's own workgroups, 8 waves per SIMD), bf16 4
+// (64 VGPRs).
 template <class T>
 constexpr int walk_group(int S) {
   return S == 1 || T::kElem == 2 ? 4 : 2;
 }
 
 // S: lane groups per vector.  One reads a whole tree where that alone gives
-// enough waves: kWalkWaves, about what the chip holds at once.  Fewer leave
-// HBM waiting, more cost an LDS exchange per vector and shorter walks.  A
-// group keeps at least kWalkSpan positions (two rounds of loads), and at most
-// what its slots hold.  Measured on MI355X, us at S = 1, 2, 4, 8, 16 (waves at
-// S = 1): N=64 bf16 32 KiB (2048) 28, 22, 23, 29, 31; N=50 float32 20 KB (976)
-// 24, 18, 12, 10.3, 13; N=500 float32 1200 B (586) -, -, 77, 56, 67; N=128
-// float32 4 KiB (512) 37, 20, 13, 12.5, 13.6.
+// enough waves: walk_waves, about what keeps HBM busy.  Fewer leave it waiting,
+// more cost an LDS exchange per vector and shorter walks.  A group keeps at
+// least kWalkSpan positions (two rounds of loads), and at most what its slots
+// hold.  Measured on MI355X, us at S = 1, 2, 4, 8, 16 (waves at S = 1):
+//   float32  N=50 20 KB (976) 17, 14, 10.5, 10.5, 12; N=500 1200 B (585) -, -,
+//            61, 56, 64; N=100 40 KB (3906) 68, 65, 64, 69, 75; N=10 1 MiB
+//            (10240) 21, 24, 26, 37, 60
+//   bf16     N=64 32 KiB (4096) 24, 25, 24, 27, 48; N=24 64 KiB (3072) 8.4, 9.3,
+//            9.6, 14, 28; N=200 666 B (262) 30, 21, 12, 9.4, 10.9
+// A bf16 walk over rows off an 8-byte boundary, whose accesses are split, is
+// faster in two parts when it is large: N=64 262143 elements 503, 432 us.
 //
 // Order of the workgroups: each XCD takes runs of `grain` consecutive blocks,
 // whose rows then cover its L2's channels evenly; one by one, blocks of 1 KiB
-// per row keep an XCD on the same few channels (N=64 bf16 32 KiB at S = 4: 35
+// per row keep an XCD on the same few channels (N=64 bf16 32 KiB at S = 4 35
 // against 23 us).  Long runs also keep an XCD on fewer pages: N=128 bf16 4 MiB
-// 13.9 ms one by one, 10.8, 10.6, 10.5, 10.4 ms with runs of 4, 16, 64, 256;
-// short ones leave a small grid balanced (N=300 float32 4 KiB, 1200 blocks: 75
-// us with runs of 4, 126 with 64).
-constexpr int64_t kWalkWaves = 4096;
+// 13.0 ms one by one, 12.0, 11.9, 11.8 ms with runs of 16, 64, 256; short ones
+// leave a small grid balanced (N=300 float32 4 KiB, 1200 blocks: 75 us with
+// runs of 4, 126 with 64).
+template <class T>
+constexpr int64_t walk_waves() {
+  return T::kElem == 2 ? 2048 : 4096;
+}
 constexpr int kWalkSpan = 8;
 constexpr int kWalkMostGroups = 16;
 
@@ -374,7 +384,9 @@ hipError_t launch_walk_rs_t(WalkCtx cx, const WalkRows& rows, hipStream_t stream
   const int64_t waves = (cx.N * cx.V + 63) / 64;
   auto holds = [&](int S) { return span / S <= walk_group<T>(S) << (walk_slots<T>(S) - 1); };
   int S = 1;
-  while (S < kWalkMostGroups && ((waves * S < kWalkWaves && span / S > kWalkSpan) || !holds(S))) S *= 2;
+  while (S < kWalkMostGroups && ((waves * S < walk_waves<T>() && span / S > kWalkSpan) || !holds(S))) S *= 2;
+  const bool split_rows = T::kElem == 2 && (!rows.aligned8 || cx.chunk_bytes % 8);
+  if (split_rows && S == 1 && waves >= 16384 && span > kWalkSpan) S = 2;
   if (!holds(S)) return hipErrorInvalidValue;
   const int threads = S <= 4 ? 256 : 64 * S;
   cx.lanes = threads / S;
@@ -552,14 +564,13 @@ hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, const WalkRows
     gx.N = cx.N;
     return launch_walk_ag(gx, rows, (int)cx.esize, stream);
   }
-  const int64_t per = 16 / cx.esize;
-  if (cx.count < kWalkLeastElems || cx.N > kWalkMostRanks) return hipErrorInvalidValue;
+    if (cx.count < kWalkLeastElems || cx.N > kWalkMostRanks) return hipErrorInvalidValue;
   WalkCtx wx{};
   wx.rows = rows_arg(cx, rows);
   wx.N = cx.N;
   wx.chunk_bytes = cx.count * cx.esize;
-  wx.V = (cx.count + per - 1) / per;
-  wx.back = (int32_t)(wx.V * per - cx.count);
+  wx.V = (cx.count + 3) / 4;
+  wx.back = (int32_t)(wx.V * 4 - cx.count);
   switch (v) {  // whichever path the plan's pieces take: a walk has none
     case kRsI32S:
     case kRsI32Vec:

@@ -7,7 +7,7 @@
 namespace pat {
 
 // Most ranks a reduce-scatter's walk holds slots for: 16 lane groups, each
-// with slots for 128 groups of 2 positions (bf16: 64 of 4).
+// with slots for 128 groups of 2 positions.
 constexpr int kWalkMostRanks = 4096;
 // Fewest elements of a chunk a walk is taken for.  Under that a tree is too
 // few vectors for a walk: N = 1000 float32 on MI355X, steps / walk, 4
@@ -23,6 +23,7 @@ struct WalkRows {
   int64_t send_stride, recv_stride;  // bytes from rank 0's buffer to rank 1's
   bool spaced;                       // every rank's buffers follow at those strides: the launch carries
                                      // two addresses and two strides
+  bool aligned8;                     // every send buffer is 8-byte aligned
   bool table;                        // neither spaced nor few enough for the launch to carry the pointers:
                                      // the kernel reads the device tables of its context
 };
@@ -31,15 +32,19 @@ struct WalkRows {
 constexpr int kWalkInlineRanks = 64;
 
 inline WalkRows walk_rows(const void* const* send, void* const* recv, int N) {
-  WalkRows w{send, recv, 0, 0, true, false};
+  WalkRows w{send, recv, 0, 0, true, true, false};
   if (N > 1) {
     const uintptr_t s0 = (uintptr_t)send[0], r0 = (uintptr_t)recv[0];
     const uintptr_t ds = (uintptr_t)send[1] - s0, dr = (uintptr_t)recv[1] - r0;
-    uintptr_t off = 0;  // any rank's distance from its place
-    for (int r = 2; r < N; ++r) off |= ((uintptr_t)send[r] - s0 - r * ds) | ((uintptr_t)recv[r] - r0 - r * dr);
+    uintptr_t off = 0, bits = s0 | (uintptr_t)send[1];
+    for (int r = 2; r < N; ++r) {
+      off |= ((uintptr_t)send[r] - s0 - r * ds) | ((uintptr_t)recv[r] - r0 - r * dr);  // distances from their places
+      bits |= (uintptr_t)send[r];
+    }
     w.send_stride = (int64_t)ds;
     w.recv_stride = (int64_t)dr;
     w.spaced = off == 0;
+    w.aligned8 = bits % 8 == 0;
   }
   w.table = !w.spaced && N > kWalkInlineRanks;
   return w;
