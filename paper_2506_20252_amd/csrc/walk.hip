@@ -159,12 +159,14 @@ template <class T, int LV>
 struct WalkSlots {
   typename T::acc_t st[LV];
 
-  // Leaf number b (0, 1, ...): merges with the sub-trees it completes.
+  // Leaf number b (0, 1, ...): merges with the sub-trees it completes.  With a
+  // key, the leaves come in the order b ^ key, which fills the same sub-trees,
+  // a level's right one first where the key has its bit.
   template <int L = 0>
-  __device__ __forceinline__ void push(int b, const typename T::acc_t& x) {
+  __device__ __forceinline__ void push(int b, const typename T::acc_t& x, int key = 0) {
     if constexpr (L < LV) {
       if ((b >> L) & 1)
-        push<L + 1>(b, T::add(st[L], x));
+        push<L + 1>(b, (key >> L) & 1 ? T::add(x, st[L]) : T::add(st[L], x), key);
       else
         st[L] = x;
     }
@@ -222,7 +224,10 @@ __device__ __forceinline__ typename T::acc_t group_sum(const typename T::in_t (&
 // adds.  The bound is HBM's read rate.  Measured on MI355X, step schedule ->
 // walk: N=64 float32 1 MiB 1992 -> 650 us, N=128 bf16 4 MiB 52.6 -> 10.8 ms
 // (6.6 and 6.4 TB/s of input), N=1000 float32 256 B 139 -> 42 us a call.
-template <class T, int G, int MAXT, int LV, bool SPLIT, bool UNI, bool SPACED, bool NT>
+//
+// KEYED (power-of-two parts only): a workgroup reads its groups of positions in
+// the order g ^ key, a key of its own.  See walk_keyed().
+template <class T, int G, int MAXT, int LV, bool SPLIT, bool UNI, bool SPACED, bool KEYED, bool NT>
 __global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkArgs<WalkCtx, SPACED> args) {
   const WalkCtx& cx = args.cx;
   using in_t = typename T::in_t;
@@ -285,14 +290,15 @@ __global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkArgs<WalkCtx, SPACED>
     auto size = [&](int g) { return n - g * G < G ? n - g * G : G; };
     WalkSlots<T, LV> slots;
     in_t x[G], y[G];
-    load(x, 0, size(0));
+    const int key = KEYED ? (int)(blk * 2654435761u >> 24) & (groups - 1) : 0;
+    load(x, key * G, size(key));
     for (int g = 0; g < groups; g += 2) {
       const bool two = g + 1 < groups;
-      if (two) load(y, (g + 1) * G, size(g + 1));
-      slots.push(g, group_sum<T, G>(x, size(g)));
+      if (two) load(y, ((g + 1) ^ key) * G, size((g + 1) ^ key));
+      slots.push(g, group_sum<T, G>(x, size(g ^ key)), key);
       if (two) {
-        if (g + 2 < groups) load(x, (g + 2) * G, size(g + 2));
-        slots.push(g + 1, group_sum<T, G>(y, size(g + 1)));
+        if (g + 2 < groups) load(x, ((g + 2) ^ key) * G, size((g + 2) ^ key));
+        slots.push(g + 1, group_sum<T, G>(y, size((g + 1) ^ key)), key);
       }
     }
     sum = slots.total(groups);
@@ -324,16 +330,22 @@ dim3 walk_grid(uint64_t blocks, uint64_t grain) {
 }
 
 template <class T, int G, int MAXT, int LV, bool SPLIT, bool NT>
-void launch_walk_rs_k(const WalkCtx& cx, const WalkRows& rows, bool uni, int threads, hipStream_t stream) {
+void launch_walk_rs_k(const WalkCtx& cx, const WalkRows& rows, bool uni, bool keyed, int threads, hipStream_t stream) {
   const dim3 grid = walk_grid(cx.blocks, cx.grain);
+  if constexpr (SPLIT && T::kElem == 4) {
+    if (keyed && uni)
+      return launch_kernel(walk_rs_kernel<T, G, MAXT, LV, true, true, true, true, NT>, grid, threads, cx, rows, stream);
+    if (keyed)
+      return launch_kernel(walk_rs_kernel<T, G, MAXT, LV, true, false, true, true, NT>, grid, threads, cx, rows, stream);
+  }
   if (rows.spaced && uni)
-    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, true, NT>, grid, threads, cx, rows, stream);
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, true, false, NT>, grid, threads, cx, rows, stream);
   else if (rows.spaced)
-    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, true, NT>, grid, threads, cx, rows, stream);
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, true, false, NT>, grid, threads, cx, rows, stream);
   else if (uni)
-    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, false, NT>, grid, threads, cx, rows, stream);
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, false, false, NT>, grid, threads, cx, rows, stream);
   else
-    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, false, NT>, grid, threads, cx, rows, stream);
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, false, false, NT>, grid, threads, cx, rows, stream);
 }
 
 // Slots of a lane group: the sub-tree it walks spans at most 2^(slots - 1)
@@ -377,6 +389,24 @@ constexpr int64_t walk_waves() {
 constexpr int kWalkSpan = 8;
 constexpr int kWalkMostGroups = 16;
 
+// Whether the parts of a tree are read in keyed orders.  Position q of chunk R
+// is at row (R + q) * spacing + R * chunk: with both sizes powers of two and
+// all workgroups at the same q, R and R + q fall on address bits that the
+// memory channels' hash combines, and the reads crowd on few channels; a key
+// per workgroup spreads q.  Measured on MI355X for float32, plain / keyed order
+// at the S in use: N=128, 16 KiB chunks (2 MiB rows) 58.6 / 44.6 us, 8 KiB 28.1
+// / 24.1, 4 KiB 15.2 / 12.3; N=1024 256 B 50.8 / 45.9; N=64 4 KiB 6.6 / 6.0;
+// N=32 16 KiB 6.1 / 6.0.  Beyond, where a workgroup's neighbours cover the
+// channels by themselves, plain order is faster: N=64 32 KiB 24.1 / 25.0, N=256
+// 16 KiB (4 MiB rows) 168 / 171, N=64 1 MiB 625 / 668, N=1024 64 B (64 KiB
+// rows) 23.6 / 27.3; so it is for rows of other spacings (N=128 16000 B 42.3 /
+// 44.0, N=100 16 KiB 27.3 / 28.2) and for bf16 (N=128 16 KiB 46.8 / 53.1).
+bool walk_keyed(const WalkCtx& cx, const WalkRows& rows) {
+  auto pow2 = [](int64_t v) { return v > 0 && (v & (v - 1)) == 0; };
+  return rows.spaced && pow2(cx.N) && pow2(rows.send_stride) && pow2(cx.chunk_bytes) && cx.chunk_bytes <= 16384 &&
+         rows.send_stride >= (256 << 10) && rows.send_stride <= (2 << 20);
+}
+
 template <class T, bool NT>
 hipError_t launch_walk_rs_t(WalkCtx cx, const WalkRows& rows, hipStream_t stream) {
   int span = 1;
@@ -399,12 +429,13 @@ hipError_t launch_walk_rs_t(WalkCtx cx, const WalkRows& rows, hipStream_t stream
   cx.tiles = (uint32_t)tiles;
   cx.blocks = (uint32_t)blocks;
   cx.grain = blocks >= 16384 ? 64 : 4;
+  const bool keyed = walk_keyed(cx, rows) && cx.w >= walk_group<T>(S);
   if (S == 1)
-    launch_walk_rs_k<T, walk_group<T>(1), 256, walk_slots<T>(1), false, NT>(cx, rows, uni, threads, stream);
+    launch_walk_rs_k<T, walk_group<T>(1), 256, walk_slots<T>(1), false, NT>(cx, rows, uni, keyed, threads, stream);
   else if (S <= 4)
-    launch_walk_rs_k<T, walk_group<T>(4), 256, walk_slots<T>(4), true, NT>(cx, rows, uni, threads, stream);
+    launch_walk_rs_k<T, walk_group<T>(4), 256, walk_slots<T>(4), true, NT>(cx, rows, uni, keyed, threads, stream);
   else
-    launch_walk_rs_k<T, walk_group<T>(16), 1024, walk_slots<T>(16), true, NT>(cx, rows, uni, threads, stream);
+    launch_walk_rs_k<T, walk_group<T>(16), 1024, walk_slots<T>(16), true, NT>(cx, rows, uni, keyed, threads, stream);
   return hipGetLastError();
 }
 

@@ -135,7 +135,8 @@ def test_overlap_checks_agree_with_the_definition():
     (200, 520, "float32", "rows"), (257, 250, "bfloat16", "rows"), (300, 75, "float32", "skewed"),
     (513, 67, "float32", "rows"), (1000, 64, "float32", "rows"), (1025, 33, "bfloat16", "rows"),
     (2049, 16, "float32", "rows"), (4096, 18, "bfloat16", "rows"), (4097, 16, "bfloat16", "rows"),
-    (31, 15, "float32", "rows"), (20, 1000, "bfloat16", "reversed"), (64, 333, "float32", "shuffled"),
+    (31, 15, "float32", "rows"), (16, 64, "float32", "rows"), (32, 1024, "int32", "rows"),
+    (128, 1024, "float32", "rows"), (64, 1024, "int32", "rows"), (1024, 64, "float32", "rows"), (20, 1000, "bfloat16", "reversed"), (64, 333, "float32", "shuffled"),
     (65, 40, "int32", "shuffled"), (300, 64, "float32", "reversed"), (600, 24, "bfloat16", "shuffled"),
 ])
 @pytest.mark.parametrize("entry", ["reducescatter", "reducescatter_noalloc"])
