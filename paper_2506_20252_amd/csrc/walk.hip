@@ -47,6 +47,20 @@ struct RowPointers {
 #define PAT_CONSTANT __attribute__((address_space(4)))
 typedef const PAT_CONSTANT uint64_t* RowTable;
 
+// The workgroups of an operation.  They go to the 8 XCDs round-robin; each XCD
+// takes runs of `grain` consecutive blocks.
+struct Blocks {
+  uint32_t count;  // in all
+  uint32_t grain;
+  uint32_t first;  // of this launch: a multiple of 8 * grain
+};
+
+// This workgroup's block; past `count`: none.
+__device__ __forceinline__ uint32_t block_of(const Blocks& b) {
+  const uint32_t x = blockIdx.x % 8, j = blockIdx.x / 8;
+  return b.first + (j / b.grain) * 8 * b.grain + x * b.grain + j % b.grain;
+}
+
 // A kernel's one argument: the pointers' place in the argument segment is
 // then known.
 template <class Ctx, bool SPACED>
@@ -77,8 +91,20 @@ __device__ __forceinline__ char* recv_row(const Ctx& cx, int r) {
   return (char*)row_table<Ctx>(cx.rows.recv_table, offsetof(RowPointers, recv))[r];
 }
 
+// Launches the blocks of cx: in one launch up to 2^31 lanes (a grid's limit is
+// 2^32 in each dimension), else in several.
+template <class Arg, class Ctx>
+void launch_blocks(void (*kernel)(Arg), int threads, Arg& arg, Ctx& cx, hipStream_t stream) {
+  const uint64_t run = 8ull * cx.blocks.grain, most = (uint64_t(1) << 31) / threads / run * run;
+  for (uint64_t first = 0; first < cx.blocks.count; first += most) {
+    const uint64_t n = std::min<uint64_t>(most, cx.blocks.count - first);
+    cx.blocks.first = (uint32_t)first;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + run - 1) / run * run)), dim3(threads), 0, stream, arg);
+  }
+}
+
 template <class Ctx, bool SPACED>
-void launch_kernel(void (*kernel)(WalkArgs<Ctx, SPACED>), dim3 grid, int threads, const Ctx& cx, const WalkRows& rows,
+void launch_kernel(void (*kernel)(WalkArgs<Ctx, SPACED>), int threads, const Ctx& cx, const WalkRows& rows,
                    hipStream_t stream) {
   WalkArgs<Ctx, SPACED> a;
   a.cx = cx;
@@ -88,7 +114,7 @@ void launch_kernel(void (*kernel)(WalkArgs<Ctx, SPACED>), dim3 grid, int threads
       std::memcpy(a.ptrs.recv, rows.recv, cx.N * sizeof(void*));
     }
   }
-  hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, a);
+  launch_blocks(kernel, threads, a, a.cx, stream);
 }
 
 // What a kernel's context says about `rows` (device tables: kx's).
@@ -96,6 +122,7 @@ RowsArg rows_arg(const KCtx& kx, const WalkRows& rows) {
   return RowsArg{(uint64_t)rows.send[0], (uint64_t)rows.recv[0], rows.send_stride, rows.recv_stride,
                  rows.table ? (uint64_t)kx.send : 0, rows.table ? (uint64_t)kx.recv : 0};
 }
+
 struct WalkCtx {
   RowsArg rows;
   int64_t chunk_bytes;      // of a user chunk
@@ -104,8 +131,8 @@ struct WalkCtx {
   int32_t back;             // a partial last vector begins this many elements inside the one before (0: none)
   int32_t w;                // positions per lane group, a power of two
   int32_t lanes;            // vectors per workgroup, a multiple of 64
-  uint32_t tiles, blocks;   // workgroups per chunk (a workgroup's vectors in one chunk), in all
-  uint32_t grain;           // consecutive blocks per XCD
+  uint32_t tiles;           // workgroups per chunk (a workgroup's vectors in one chunk)
+  Blocks blocks;
 };
 
 // A chunk's vectors are read at element alignment (see Access); the last one
@@ -239,11 +266,8 @@ __global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkArgs<WalkCtx, SPACED>
     s = __builtin_amdgcn_readfirstlane(threadIdx.x / lanes);
     lane = threadIdx.x - s * lanes;
   }
-  // Workgroups go to the 8 XCDs round-robin; each XCD takes runs of `grain`
-  // consecutive blocks.
-  const uint32_t x8 = blockIdx.x % 8, j8 = blockIdx.x / 8;
-  const uint32_t blk = (j8 / cx.grain) * 8 * cx.grain + x8 * cx.grain + j8 % cx.grain;
-  if (blk >= cx.blocks) return;
+  const uint32_t blk = block_of(cx.blocks);
+  if (blk >= cx.blocks.count) return;
   int R;
   int64_t v;
   bool live;
@@ -324,28 +348,22 @@ __global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkArgs<WalkCtx, SPACED>
     stg<NT, T::kElem>(dst, out);
 }
 
-// Grid of `blocks` workgroups in XCD runs of `grain`.
-dim3 walk_grid(uint64_t blocks, uint64_t grain) {
-  return dim3((unsigned)((blocks + 8 * grain - 1) / (8 * grain) * (8 * grain)));
-}
-
 template <class T, int G, int MAXT, int LV, bool SPLIT, bool NT>
 void launch_walk_rs_k(const WalkCtx& cx, const WalkRows& rows, bool uni, bool keyed, int threads, hipStream_t stream) {
-  const dim3 grid = walk_grid(cx.blocks, cx.grain);
   if constexpr (SPLIT && T::kElem == 4) {
     if (keyed && uni)
-      return launch_kernel(walk_rs_kernel<T, G, MAXT, LV, true, true, true, true, NT>, grid, threads, cx, rows, stream);
+      return launch_kernel(walk_rs_kernel<T, G, MAXT, LV, true, true, true, true, NT>, threads, cx, rows, stream);
     if (keyed)
-      return launch_kernel(walk_rs_kernel<T, G, MAXT, LV, true, false, true, true, NT>, grid, threads, cx, rows, stream);
+      return launch_kernel(walk_rs_kernel<T, G, MAXT, LV, true, false, true, true, NT>, threads, cx, rows, stream);
   }
   if (rows.spaced && uni)
-    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, true, false, NT>, grid, threads, cx, rows, stream);
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, true, false, NT>, threads, cx, rows, stream);
   else if (rows.spaced)
-    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, true, false, NT>, grid, threads, cx, rows, stream);
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, true, false, NT>, threads, cx, rows, stream);
   else if (uni)
-    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, false, false, NT>, grid, threads, cx, rows, stream);
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, true, false, false, NT>, threads, cx, rows, stream);
   else
-    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, false, false, NT>, grid, threads, cx, rows, stream);
+    launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, false, false, NT>, threads, cx, rows, stream);
 }
 
 // Slots of a lane group: the sub-tree it walks spans at most 2^(slots - 1)
@@ -425,10 +443,9 @@ hipError_t launch_walk_rs_t(WalkCtx cx, const WalkRows& rows, hipStream_t stream
   // A chunk's vectors fill its own workgroups unless that leaves too many lanes idle.
   const bool uni = tiles * cx.lanes <= cx.V + cx.V / 8;
   const int64_t blocks = uni ? tiles * cx.N : (cx.N * cx.V + cx.lanes - 1) / cx.lanes;
-  if (blocks > (int64_t(1) << 30)) return hipErrorInvalidValue;
+  if (blocks > (int64_t(1) << 31)) return hipErrorInvalidValue;
   cx.tiles = (uint32_t)tiles;
-  cx.blocks = (uint32_t)blocks;
-  cx.grain = blocks >= 16384 ? 64 : 4;
+  cx.blocks = {(uint32_t)blocks, blocks >= 16384 ? 64u : 4u, 0};
   const bool keyed = walk_keyed(cx, rows) && cx.w >= walk_group<T>(S);
   if (S == 1)
     launch_walk_rs_k<T, walk_group<T>(1), 256, walk_slots<T>(1), false, NT>(cx, rows, uni, keyed, threads, stream);
@@ -454,8 +471,8 @@ struct GatherCtx {
   int32_t N;
   int32_t period;           // rows r and r + period start at the same offset from a 128-byte line
   int32_t run;              // receivers per workgroup, `period` apart
-  uint32_t tiles, blocks;   // tiles per row, workgroups in all
-  uint32_t grain;           // consecutive blocks per XCD
+  uint32_t tiles;           // tiles per row
+  Blocks blocks;
 };
 
 constexpr int kGatherThreads = 256;
@@ -469,17 +486,16 @@ constexpr int kGatherTile = kGatherThreads * 16;  // bytes
 // bytes from its row's start.  Vectors that hold bytes of several chunks, and
 // the row's ends, are read and where necessary stored element by element.
 // ES: bytes per element.
-// Measured on MI355X, step schedule -> walk: N=128 float32 1 MiB 7062 -> 2830
-// us, N=1000 float32 256 B 114 -> 57 us, 252 B 148 -> 52 us, N=24 bf16 64 KiB
-// 28 -> 21 us a call.
+// Measured on MI355X, step schedule -> walk, a call: N=128 float32 1 MiB 7062 ->
+// 2940 us, N=1000 float32 252 B 148 -> 38 us, N=13 bf16 2002 B in place 23 -> 4.5
+// us.
 template <int ES, bool SPACED>
 __global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(WalkArgs<GatherCtx, SPACED> args) {
   const GatherCtx& cx = args.cx;
   constexpr int kElems = 16 / ES;
   using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
-  const uint32_t x8 = blockIdx.x % 8, j8 = blockIdx.x / 8;
-  const uint32_t blk = (j8 / cx.grain) * 8 * cx.grain + x8 * cx.grain + j8 % cx.grain;
-  if (blk >= cx.blocks) return;
+  const uint32_t blk = block_of(cx.blocks);
+  if (blk >= cx.blocks.count) return;
   const uint32_t g = blk / cx.tiles, tile = blk - g * cx.tiles;
   // receivers r0, r0 + period, ...: `run` of them
   const int turn = (int)g / cx.period, r0 = (int)g - turn * cx.period + turn * cx.run * cx.period;
@@ -562,19 +578,83 @@ hipError_t launch_walk_ag(GatherCtx cx, const WalkRows& rows, int esize, hipStre
   cx.run = (int32_t)std::min<int64_t>(kGatherRun, (tiles * cx.N + kGatherBlocks - 1) / kGatherBlocks);
   const int64_t turns = ((cx.N + cx.period - 1) / cx.period + cx.run - 1) / cx.run;
   const int64_t blocks = tiles * turns * cx.period;
-  if (blocks > (int64_t(1) << 30)) return hipErrorInvalidValue;
+  if (blocks > (int64_t(1) << 31)) return hipErrorInvalidValue;
   cx.tiles = (uint32_t)tiles;
-  cx.blocks = (uint32_t)blocks;
   // Order: tiles of the same receivers follow each other.  Runs of them per
   // XCD for large operations only (N=128 float32 1 MiB, 1.05 M blocks: 2967 us
   // one by one, 2880 us with runs of 256; N=300 4 KiB, 22500: 56 and 64 us).
-  cx.grain = blocks >= (1 << 18) ? 256 : 1;
-  const dim3 grid = walk_grid(cx.blocks, cx.grain);
+  cx.blocks = {(uint32_t)blocks, blocks >= (1 << 18) ? 256u : 1u, 0};
   if (rows.spaced)
-    launch_kernel(esize == 2 ? walk_ag_kernel<2, true> : walk_ag_kernel<4, true>, grid, kGatherThreads, cx, rows, stream);
+    launch_kernel(esize == 2 ? walk_ag_kernel<2, true> : walk_ag_kernel<4, true>, kGatherThreads, cx, rows, stream);
   else
-    launch_kernel(esize == 2 ? walk_ag_kernel<2, false> : walk_ag_kernel<4, false>, grid, kGatherThreads, cx, rows,
-                  stream);
+    launch_kernel(esize == 2 ? walk_ag_kernel<2, false> : walk_ag_kernel<4, false>, kGatherThreads, cx, rows, stream);
+  return hipGetLastError();
+}
+
+// Send buffers that follow each other (the rows of one tensor): the
+// concatenation is in memory already, and a receiver's row is a copy of it.  A
+// lane copies one vector to one receiver: with nothing to look up and no vector
+// across chunks, short workgroups stream best, and the receivers of a tile
+// come by the order of the workgroups instead of in a loop.  Tiles start at
+// the receiver's 128-byte lines as above.
+struct CopyCtx {
+  uint64_t send0, recv0;
+  int64_t recv_stride, row_bytes;
+  uint32_t N;
+  uint32_t panel;  // tiles that every receiver takes before the next ones
+  Blocks blocks;
+};
+
+template <int ES>
+__global__ __launch_bounds__(kGatherThreads) void walk_ag_rows_kernel(CopyCtx cx) {
+  using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
+  const uint32_t blk = block_of(cx.blocks);
+  if (blk >= cx.blocks.count) return;
+  const uint32_t g = blk / cx.panel;  // (panel, receiver, tile of the panel)
+  const uint32_t p = g / cx.N, tile = p * cx.panel + (blk - g * cx.panel);
+  char* const row = (char*)(cx.recv0 + (uint64_t)((int64_t)(g - p * cx.N) * cx.recv_stride));
+  const char* const src = (const char*)cx.send0;
+  const int64_t tile0 = (int64_t)tile * kGatherTile - (int64_t)((uintptr_t)row & 127);  // may be negative
+  const int64_t o = tile0 + (int)threadIdx.x * 16;
+  if (o >= 0 && o + 16 <= cx.row_bytes) {
+    stg<true, ES>(row + o, ldg<v4u, false, ES>(src + o));
+  } else {  // the row's ends
+    for (int64_t i = o < 0 ? 0 : o; i < o + 16 && i < cx.row_bytes; i += ES)
+      stg<false>(row + i, ldg<elem_t, false>(src + i));
+  }
+}
+
+// Order of the workgroups.  A panel of the concatenation (at most kCopyPanel
+// tiles, 2 MiB) goes to every receiver before the next panel, and an XCD takes
+// the same eighth of it for each of them: its L2 then serves the panel's reads
+// but the first.  Measured on MI355X, us with the tiles of four receivers in a
+// loop (walk_ag_kernel) / in this order: N=128 float32 1 MiB 2937 / 2449 (7.0
+// TB/s written), N=700 bf16 32 KiB 2745 / 2239, N=128 bf16 262143 elements 1470 /
+// 1178, N=50 float32 400 KB 177 / 142, N=8 bf16 1000001 elements 29 / 20, N=24
+// bf16 64 KiB 8.5 / 7.6.  With XCD runs that do not repeat from one receiver to
+// the next: 2600, 2333, 1231, 157, 33, 8.2.  A concatenation under
+// kCopyLeastPanels tiles is in every L2 soon; there longer runs across the
+// receivers' rows are faster (N=5000 float32 64 B: 220 against 267 us, loop 265;
+// N=1024 bf16 38 B 7.9, 11.4, 10.6; N=100 bf16 6666 B 10.9, 12.0, 14.0; N=1000
+// float32 256 B 39, 37, 42).
+constexpr int64_t kCopyPanel = 512;
+constexpr int64_t kCopyLeastPanels = 256;
+
+hipError_t launch_walk_ag_rows(const GatherCtx& gx, const WalkRows& rows, int esize, hipStream_t stream) {
+  CopyCtx cx{(uint64_t)rows.send[0], (uint64_t)rows.recv[0], rows.recv_stride, gx.row_bytes, (uint32_t)gx.N, 0, {}};
+  // a tile more for rows that start up to 127 bytes past a line
+  const int64_t tiles = (gx.row_bytes + 127 + kGatherTile - 1) / kGatherTile;
+  const int64_t panels = (tiles + kCopyPanel - 1) / kCopyPanel;
+  int64_t grain = ((tiles + panels - 1) / panels + 7) / 8;
+  cx.panel = (uint32_t)(8 * grain);
+  if (tiles < kCopyLeastPanels) {
+    cx.panel = (uint32_t)tiles;
+    grain = tiles * gx.N >= 65536 ? 64 : 16;
+  }
+  const int64_t blocks = panels * cx.panel * gx.N;
+  if (blocks > (int64_t(1) << 31)) return hipErrorInvalidValue;
+  cx.blocks = {(uint32_t)blocks, (uint32_t)grain, 0};
+  launch_blocks(esize == 2 ? walk_ag_rows_kernel<2> : walk_ag_rows_kernel<4>, kGatherThreads, cx, cx, stream);
   return hipGetLastError();
 }
 
@@ -593,6 +673,7 @@ hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, const WalkRows
     gx.chunk_bytes = cx.count * cx.esize;
     gx.row_bytes = cx.N * gx.chunk_bytes;
     gx.N = cx.N;
+    if (rows.spaced && rows.send_stride == gx.chunk_bytes) return launch_walk_ag_rows(gx, rows, (int)cx.esize, stream);
     return launch_walk_ag(gx, rows, (int)cx.esize, stream);
   }
     if (cx.count < kWalkLeastElems || cx.N > kWalkMostRanks) return hipErrorInvalidValue;

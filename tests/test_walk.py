@@ -248,3 +248,38 @@ def test_walked_allgather(n, count, dtype, layout):
     bad = [r for r in range(n) if not torch.equal(recv[r].view(torch.uint8), want.view(torch.uint8))]
     assert not bad, bad[:8]
     assert torch.equal(whole[mark], outside)
+
+
+@pytest.mark.gpu
+def test_walks_beyond_one_grid():
+    """Operations of more workgroups than one grid takes (2^31 lanes) run as
+    several launches: an all-gather into 40 GiB and a reduce-scatter of 2 ranks
+    with more than 2^31 vectors, against plain torch."""
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream()
+    pat.check(pat.pat_set_exec_mode("stream"))
+    pat.check(pat.pat_finalize())
+    n, count = 200, 262144
+    print(f"[gpu] walk allgather n={n} count={count} float32 (40 GiB)", file=sys.stderr, flush=True)
+    send = torch.randn(n, count, device=dev)
+    recv = torch.empty(n, n * count, device=dev)
+    pat.check(pat.pat_allgather(list(send), list(recv), count, "float32", n, stream))
+    torch.cuda.synchronize()
+    assert not [r for r in range(n) if not torch.equal(recv[r], send.reshape(-1))]
+    del send, recv
+    pat.check(pat.pat_finalize())
+    torch.cuda.empty_cache()
+    n, count = 2, 4 * (1 << 30) + 1027
+    print(f"[gpu] walk reducescatter n={n} count={count} float32", file=sys.stderr, flush=True)
+    send = torch.empty(n, n * count, device=dev).uniform_(-1, 1)
+    recv = torch.empty(n, count, device=dev)
+    pat.check(pat.pat_reducescatter(list(send), list(recv), count, "float32", pat.PAT_SUM, n, stream))
+    torch.cuda.synchronize()
+    step = 1 << 28
+    for r in range(n):
+        for i in range(0, count, step):
+            j = min(i + step, count)
+            assert torch.equal(recv[r, i:j], send[r, r * count + i:r * count + j] + send[1 - r, r * count + i:r * count + j])
+    del send, recv
+    pat.check(pat.pat_finalize())
+    torch.cuda.empty_cache()
