@@ -676,7 +676,7 @@ hipError_t launch_walk(Variant v, bool streaming, const KCtx& cx, const WalkRows
     if (rows.spaced && rows.send_stride == gx.chunk_bytes) return launch_walk_ag_rows(gx, rows, (int)cx.esize, stream);
     return launch_walk_ag(gx, rows, (int)cx.esize, stream);
   }
-    if (cx.count < kWalkLeastElems || cx.N > kWalkMostRanks) return hipErrorInvalidValue;
+  if (cx.count < kWalkLeastElems || cx.N > kWalkMostRanks) return hipErrorInvalidValue;
   WalkCtx wx{};
   wx.rows = rows_arg(cx, rows);
   wx.N = cx.N;
