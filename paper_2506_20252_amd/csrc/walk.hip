@@ -393,6 +393,13 @@ constexpr int walk_group(int S) {
 // A bf16 walk over rows off an 8-byte boundary, whose accesses are split, is
 // faster in two parts when it is large: N=64 262143 elements 503, 432 us.
 //
+// Workgroups of 256 lanes.  For large whole-tree walks wider ones are slower and
+// narrower ones no different, us at 256 lanes / at another width, side by side:
+//   N=64 float32 1 MiB    64: 653, 648   128: 657, 634   512: 640, 705   1024: 657, 700
+//   N=128 bf16 4 MiB, ms  64: 10.7, 10.6 128: 10.3, 10.5 512: 10.6, 10.7 1024: 10.7, 11.0
+//   N=64 float32 262143   64: 692, 682   128: 675, 687   512: 682, 745   1024: 681, 739
+// (two runs of one width differ by up to 4%, once 6%).
+//
 // Order of the workgroups: each XCD takes runs of `grain` consecutive blocks,
 // whose rows then cover its L2's channels evenly; one by one, blocks of 1 KiB
 // per row keep an XCD on the same few channels (N=64 bf16 32 KiB at S = 4 35
