@@ -789,7 +789,7 @@ double launch_bytes(const HostPlan& h, int vi, int s) {
 bool step_schedule_asked() {
   static const char* const names[] = {"WALK=0",          "TREE_TILE=", "TREE_FUSE_VECS=", "TREE_FUSE_BYTES=",
                                       "TREE_EDGE_CACHE=", "XCD_GRAIN=", "STREAMING=",      "PIECE_PIPELINE="};
-  for (char** e = environ; *e; ++e) {
+  for (char** e = environ; e && *e; ++e) {  // null without any environment (clearenv)
     if (std::strncmp(*e, "PAT_", 4)) continue;
     for (const char* n : names)
       if (!std::strncmp(*e + 4, n, std::strlen(n))) return true;

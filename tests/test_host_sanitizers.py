@@ -50,6 +50,31 @@ def test_abi_host_paths_under_asan_ubsan(tmp_path):
     assert "plans checked, 0 failures" in res.stdout
 
 
+@pytest.fixture(scope="module")
+def call_check(tmp_path_factory):
+    """The C-ABI layer over a stand-in for the HIP runtime (tests/host/hip_fake.hpp)."""
+    if shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include/hip"):
+        pytest.skip("no g++ or no HIP headers")
+    exe = tmp_path_factory.mktemp("call_check") / "call_check"
+    csrc = os.path.join(ROOT, "paper_2506_20252_amd", "csrc")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+           "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", csrc, os.path.join(csrc, "api.cpp"),
+           os.path.join(csrc, "plan.cpp"), os.path.join(ROOT, "tests", "host", "call_check.cpp"), "-o", str(exe)]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-3000:]
+    return str(exe)
+
+
+@pytest.mark.parametrize("check", ["no_environment"])
+def test_whole_calls_over_a_fake_runtime(call_check, check):
+    """Whole calls on the CPU, with the launches they make and the addresses
+    those find.  no_environment: a process without any environment."""
+    env = {k: v for k, v in os.environ.items() if not k.startswith("PAT_")}
+    res = subprocess.run([call_check, check], capture_output=True, text=True, timeout=600, env=env)
+    assert res.returncode == 0, (res.stdout[-1000:], res.stderr[-3000:])
+    assert f"{check}: 0 failures" in res.stdout
+
+
 @pytest.mark.skipif(shutil.which("g++") is None, reason="no g++")
 @pytest.mark.parametrize("sanitizer", ["address,undefined", "thread"])
 def test_threaded_oracle_under_sanitizers(tmp_path, sanitizer):
