@@ -821,9 +821,7 @@ hipError_t enqueue_walk(const HostPlan& h, pat_dtype_t dt, int vi, const pat::KC
                         hipStream_t q) {
   const pat::PlanDesc& d = h.desc;
   const double input = double(d.N) * d.N * double(d.count) * d.esize_in;
-  pat::TreeRange tr{};
-  tr.walk = &rows;
-  return pat::launch_tree(variant_for(d.coll, dt, vi), input >= kWalkStreamingBytes, cx, tr, q);
+  return pat::launch_walk(variant_for(d.coll, dt, vi), input >= kWalkStreamingBytes, cx, rows, q);
 }
 
 // Stream-mode launch sequence: one kernel per step, except that the fused

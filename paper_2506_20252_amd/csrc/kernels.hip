@@ -51,7 +51,6 @@
 
 #include "device_access.hpp"
 #include "kernels.hpp"
-#include "walk.hpp"
 
 // Tuning knobs (compile time): vectors in flight per lane.  Whether loads and
 // stores stream (nontemporal) and the work-item order are launch arguments,
@@ -1392,7 +1391,6 @@ hipError_t launch_tree_t(const KCtx& cx, const TreeRange& tr, hipStream_t stream
 }
 
 hipError_t launch_tree(Variant v, bool streaming, const KCtx& cx, const TreeRange& tr, hipStream_t stream) {
-  if (tr.walk) return launch_walk(v, streaming, cx, *tr.walk, stream);
 #define PAT_TREE(OP) launch_tree_t<PAT_UNPAREN OP>(cx, tr, stream)
   PAT_DISPATCH(v, streaming, PAT_TREE)
 #undef PAT_TREE

@@ -111,9 +111,6 @@ struct TreeRange {
   int32_t c0, c1;
   int32_t cn, ce0;
   int16_t cend[kTreeCacheSteps];
-  // Not null: the whole operation as one walk launch over these buffers
-  // (walk.hpp); the fields above are unused.  Host memory.
-  const struct WalkRows* walk;
 };
 hipError_t launch_tree(Variant v, bool streaming, const KCtx& cx, const TreeRange& tr, hipStream_t stream);
 // Persistent execution: one launch of `grid` workgroups that take per-step

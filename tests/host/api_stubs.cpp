@@ -1,9 +1,10 @@
-// Host-only stand-ins for the kernel entry points of kernels.hip, so that the
-// C-ABI layer (api.cpp) can be built with g++ under the sanitizers.  Launches
-// do nothing and succeed: no kernel runs, so nothing ever reads the fake
-// buffer addresses the checks use.  The sizes follow kernels.hip's variants;
-// they only shape the launch-level steps the host code builds.
+// Host-only stand-ins for the kernel entry points of kernels.hip and walk.hip,
+// so that the C-ABI layer (api.cpp) can be built with g++ under the sanitizers.
+// Launches do nothing and succeed: no kernel runs, so nothing ever reads the
+// fake buffer addresses the checks use.  The sizes follow kernels.hip's
+// variants; they only shape the launch-level steps the host code builds.
 #include "kernels.hpp"
+#include "walk.hpp"
 
 namespace pat {
 
@@ -22,6 +23,7 @@ int variant_pack_tile(Variant v) { return v == kAgS4 || v == kAgS2 || v == kRsI3
 
 hipError_t launch_step(Variant, bool, int64_t, const KCtx&, const DevStep&, hipStream_t) { return hipSuccess; }
 hipError_t launch_tree(Variant, bool, const KCtx&, const TreeRange&, hipStream_t) { return hipSuccess; }
+hipError_t launch_walk(Variant, bool, const KCtx&, const WalkRows&, hipStream_t) { return hipSuccess; }
 hipError_t launch_step2(Variant, bool, int64_t, const KCtx&, int, const DevStep&, int, const DevStep&, hipStream_t) {
   return hipSuccess;
 }

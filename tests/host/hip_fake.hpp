@@ -169,8 +169,11 @@ hipError_t launch_step2(Variant, bool nt, int64_t, const KCtx& cx, int, const De
                         hipStream_t) {
   return fake::launch('s', nt, cx), hipSuccess;
 }
-hipError_t launch_tree(Variant, bool nt, const KCtx& cx, const TreeRange& tr, hipStream_t) {
-  return fake::launch(tr.walk ? 'w' : 't', nt, cx, tr.walk), hipSuccess;
+hipError_t launch_tree(Variant, bool nt, const KCtx& cx, const TreeRange&, hipStream_t) {
+  return fake::launch('t', nt, cx), hipSuccess;
+}
+hipError_t launch_walk(Variant, bool nt, const KCtx& cx, const WalkRows& rows, hipStream_t) {
+  return fake::launch('w', nt, cx, &rows), hipSuccess;
 }
 hipError_t launch_persistent(Variant, bool nt, const KCtx& cx, int, hipStream_t) {
   return fake::launch('p', nt, cx), hipSuccess;
