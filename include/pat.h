@@ -245,10 +245,10 @@ int pat_get_exec_mode(void);
  * and stores it to several ranks, as every node of a chunk's tree forwards the
  * bytes it received.  Results and the summation order are the same; the buffer
  * budget, pieces and the aggregation rule, which shape the step schedule, do
- * not change a walk.  The step schedule runs instead while a launch trace is
- * armed, for plans with a step clock, and when the environment has PAT_WALK=0
- * or one of the step kernels' tuning variables (PAT_TREE_*, PAT_XCD_GRAIN,
- * PAT_STREAMING, PAT_PIECE_PIPELINE).
+ * not change a walk.  The step schedule runs instead while a trace of it is
+ * armed (pat_trace_start), for plans with a step clock, and when the environment
+ * has PAT_WALK=0 or one of the step kernels' tuning variables (PAT_TREE_*,
+ * PAT_XCD_GRAIN, PAT_STREAMING, PAT_PIECE_PIPELINE).
  */
 typedef enum { PAT_FUSION_AUTO = 0, PAT_FUSION_OFF = 1, PAT_FUSION_ON = 2 } pat_fusion_t;
 pat_status_t pat_set_top_fusion(int mode);
@@ -315,24 +315,28 @@ pat_status_t pat_plan_steps(pat_collective_t coll, int nranks, size_t count, pat
                             int* nentries);
 
 /*
- * Launch tracing of the step schedule, for measurement (stream mode only; graph
- * and persistent modes and pat_reducescatter_noalloc record nothing).  While a
- * trace is armed, operations run their steps, never a walk launch.
- * pat_trace_start
- * creates 2 * max_launches HIP events and arms the trace: the following
- * operations record one event on their stream right before and one right
- * after each kernel launch, until max_launches launches are recorded.
+ * Launch tracing, for measurement (stream mode only; graph and persistent modes
+ * and pat_reducescatter_noalloc record nothing).  Both starts create
+ * 2 * max_launches HIP events and arm the trace: the following operations
+ * record one event on their stream right before and one right after each
+ * kernel launch, until max_launches launches are recorded.  With
+ * pat_trace_start_as_run operations run as they do untraced; with
+ * pat_trace_start they run their steps, never a walk launch, so that the
+ * schedule can be measured launch by launch.
  * pat_trace_read waits for the recorded events and returns, per launch in
- * launch order: its duration in milliseconds (ms), the algorithmic bytes it
- * moves by the plan's byte model (bytes; summed over an operation's launches
- * they give pat_plan_info's alg_bytes), its kernel (kind: 0 one step, 1 a
- * fused range of steps) and its first launch-level step (step).  Any output
+ * launch order: its duration in milliseconds (ms); the bytes it moves (bytes:
+ * by the plan's byte model, which summed over the launches of an operation's
+ * steps gives pat_plan_info's alg_bytes; of a walk, each input read once and
+ * each output written once); its kernel (kind: 0 one step, 1 a fused range of
+ * steps, 2 a walk, which one record covers also where it takes several grids)
+ * and its first launch-level step (step; 0 of a walk).  Any output
  * array may be NULL; each must hold `max` entries.  *n gets the number of
  * launches recorded; if it exceeds max, PAT_ERR_INVALID_ARGUMENT and the trace
  * stays armed.  Otherwise the events are destroyed and the trace disarmed.
  * max_launches: 1 .. 2^20.
  */
 pat_status_t pat_trace_start(int max_launches);
+pat_status_t pat_trace_start_as_run(int max_launches);
 pat_status_t pat_trace_read(float* ms, double* bytes, int32_t* kind, int32_t* step, int max, int* n);
 
 /*

@@ -752,16 +752,18 @@ pat::TreeRange tree_range(const HostPlan& h, int vi) {
   return tr;
 }
 
-// Launch tracing (pat_trace_start / pat_trace_read): a HIP event pair around
-// each kernel launch of stream-mode operations, with the launch's algorithmic
-// bytes, until `max` launches are recorded.  Guarded by g_mu.
+// Launch tracing (pat_trace_start / pat_trace_start_as_run / pat_trace_read):
+// a HIP event pair around each kernel launch of stream-mode operations, with
+// the launch's algorithmic bytes, until `max` launches are recorded.  Guarded
+// by g_mu.
 struct Trace {
   bool armed = false;
+  bool steps = false;          // traced operations run their steps, never a walk
   int max = 0, used = 0;
   std::vector<hipEvent_t> ev;  // [2 * max]: before / after launch j
   std::vector<double> bytes;   // [max]
-  std::vector<int32_t> kind;   // [max]: 0 step kernel, 1 fused range
-  std::vector<int32_t> step;   // [max]: launch-level step (the first of a fused range)
+  std::vector<int32_t> kind;   // [max]: 0 step kernel, 1 fused range, 2 walk
+  std::vector<int32_t> step;   // [max]: launch-level step (the first of a fused range; 0 for a walk)
 
   void clear() {
     for (hipEvent_t e : ev)
@@ -770,7 +772,7 @@ struct Trace {
     bytes.clear();
     kind.clear();
     step.clear();
-    armed = false;
+    armed = steps = false;
     max = used = 0;
   }
 };
@@ -818,10 +820,24 @@ bool walk_applies(const HostPlan& h) {
 }
 
 hipError_t enqueue_walk(const HostPlan& h, pat_dtype_t dt, int vi, const pat::KCtx& cx, const pat::WalkRows& rows,
-                        hipStream_t q) {
+                        hipStream_t q, Trace* trace = nullptr) {
   const pat::PlanDesc& d = h.desc;
-  const double input = double(d.N) * d.N * double(d.count) * d.esize_in;
-  return pat::launch_walk(variant_for(d.coll, dt, vi), input >= kWalkStreamingBytes, cx, rows, q);
+  const double chunk = double(d.count) * d.esize_in, input = double(d.N) * d.N * chunk;
+  const bool traced = trace && trace->used < trace->max;
+  if (traced) {
+    const hipError_t e = hipEventRecord(trace->ev[2 * trace->used], q);
+    if (e != hipSuccess) return e;
+  }
+  hipError_t e = pat::launch_walk(variant_for(d.coll, dt, vi), input >= kWalkStreamingBytes, cx, rows, q);
+  if (e != hipSuccess || !traced) return e;
+  const int j = trace->used;
+  e = hipEventRecord(trace->ev[2 * j + 1], q);
+  if (e != hipSuccess) return e;
+  trace->bytes[j] = input + d.N * chunk;  // each input read once, each output written once
+  trace->kind[j] = 2;
+  trace->step[j] = 0;
+  trace->used = j + 1;
+  return hipSuccess;
 }
 
 // Stream-mode launch sequence: one kernel per step, except that the fused
@@ -929,7 +945,7 @@ pat_status_t run(int coll, const void* const* send, void* const* recv, size_t co
 
   const int mode = mode_now();
   const pat::WalkRows rows = pat::walk_rows(send, recv, N);
-  const bool walk = mode == PAT_EXEC_STREAM && !g_trace.armed && !plan->step_clock && walk_applies(h);
+  const bool walk = mode == PAT_EXEC_STREAM && !g_trace.steps && !plan->step_clock && walk_applies(h);
   // A walk whose launch carries the buffers' addresses uses nothing of the
   // plan's device memory.
   const bool on_device = !walk || rows.table;
@@ -971,7 +987,7 @@ pat_status_t run(int coll, const void* const* send, void* const* recv, size_t co
   const pat::Variant var = variant_for(coll, dt, vi);
   const auto& steps = h.steps[vi];
   if (walk) {
-    HIP_TRY(enqueue_walk(h, dt, vi, cx, rows, stream));
+    HIP_TRY(enqueue_walk(h, dt, vi, cx, rows, stream, g_trace.armed ? &g_trace : nullptr));
   } else if (mode == PAT_EXEC_DATAFLOW) {
     // The relaxed bf16 reduce-scatter gives partial vectors work items of
     // their own, spanning many edges: dataflow runs its element-wide twin.
@@ -1356,7 +1372,11 @@ pat_status_t pat_plan_steps(pat_collective_t coll, int nranks, size_t count, pat
   return PAT_OK;
 }
 
-pat_status_t pat_trace_start(int max_launches) {
+}  // extern "C"
+
+namespace {
+
+pat_status_t trace_start(int max_launches, bool steps) {
   if (max_launches < 1 || max_launches > (1 << 20)) return PAT_ERR_INVALID_ARGUMENT;
   std::lock_guard<std::mutex> lock(g_mu);
   g_trace.clear();
@@ -1376,8 +1396,17 @@ pat_status_t pat_trace_start(int max_launches) {
   g_trace.step.assign(max_launches, 0);
   g_trace.max = max_launches;
   g_trace.armed = true;
+  g_trace.steps = steps;
   return PAT_OK;
 }
+
+}  // namespace
+
+extern "C" {
+
+pat_status_t pat_trace_start(int max_launches) { return trace_start(max_launches, true); }
+
+pat_status_t pat_trace_start_as_run(int max_launches) { return trace_start(max_launches, false); }
 
 pat_status_t pat_trace_read(float* ms, double* bytes, int32_t* kind, int32_t* step, int max, int* n) {
   if (!n) return PAT_ERR_INVALID_ARGUMENT;

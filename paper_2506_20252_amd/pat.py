@@ -64,7 +64,8 @@ EXPORTS = (
     "pat_set_exec_mode", "pat_get_exec_mode", "pat_set_linear_order", "pat_get_linear_order",
     "pat_set_top_fusion", "pat_get_top_fusion", "pat_set_aggregation", "pat_get_aggregation",
     "pat_set_barrier_timeout_us", "pat_plan_info",
-    "pat_plan_steps", "pat_trace_start", "pat_trace_read", "pat_step_clock", "pat_cache_stats",
+    "pat_plan_steps", "pat_trace_start", "pat_trace_start_as_run", "pat_trace_read", "pat_step_clock",
+    "pat_cache_stats",
     "pat_check_device_status", "pat_last_hip_error", "pat_status_string",
     "pat_finalize",
 )
@@ -128,6 +129,7 @@ def lib():
                                 ctypes.c_int, _I32P, _I32P, _I32P, _I32P, ctypes.c_int,
                                 ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)], ctypes.c_int),
             "pat_trace_start": ([ctypes.c_int], ctypes.c_int),
+            "pat_trace_start_as_run": ([ctypes.c_int], ctypes.c_int),
             "pat_trace_read": ([ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_double), _I32P, _I32P,
                                 ctypes.c_int, ctypes.POINTER(ctypes.c_int)], ctypes.c_int),
             "pat_step_clock": ([ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int,
@@ -356,6 +358,10 @@ def pat_plan_steps(coll, nranks, count, dtype):
 
 def pat_trace_start(max_launches):
     return lib().pat_trace_start(int(max_launches))
+
+
+def pat_trace_start_as_run(max_launches):
+    return lib().pat_trace_start_as_run(int(max_launches))
 
 
 def pat_trace_read(max_launches):

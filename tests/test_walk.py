@@ -175,6 +175,29 @@ def test_walked_reducescatter(n, count, dtype, layout, entry):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("coll", ["allgather", "reducescatter"])
+def test_trace_as_run_times_the_walk(coll):
+    """pat_trace_start_as_run records the launch an untraced call makes: one
+    walk, with the bytes it needs."""
+    n, count = 24, 32768
+    print(f"[gpu] trace as run {coll} n={n} count={count}", file=sys.stderr, flush=True)
+    pat.check(pat.pat_set_exec_mode("stream"))
+    stream = torch.cuda.current_stream()
+    s_elems, r_elems = (count, n * count) if coll == "allgather" else (n * count, count)
+    send, recv = rows(n, s_elems, "float32", "rows"), rows(n, r_elems, "float32", "rows")
+    for x in range(n):
+        synth.fill(send[x], "f32_normal", 3, x)
+    args = (count, "float32") if coll == "allgather" else (count, "float32", pat.PAT_SUM)
+    pat.check(pat.pat_trace_start_as_run(3))
+    for _ in range(3):
+        pat.check(getattr(pat, "pat_" + coll)(send, recv, *args, n, stream))
+    st, launches = pat.pat_trace_read(3)
+    pat.check(st)
+    assert [(b, k, s) for _, b, k, s in launches] == [(4.0 * count * n * (n + 1), 2, 0)] * 3
+    assert all(ms > 0 for ms, _, _, _ in launches)
+
+
+@pytest.mark.gpu
 def test_walk_over_a_pointer_table_is_not_the_slower_path(monkeypatch):
     """Rows at no regular spacing, more ranks than a launch carries pointers
     for, chunks that share a workgroup: a walk takes no longer than the step
