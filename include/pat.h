@@ -285,7 +285,8 @@ typedef struct {
   double bus_bytes_per_rank;  /* (nranks - 1) * count * sizeof(dtype) */
   int fused_steps;            /* steps the schedule runs as one fused launch (stream/graph modes, current setting) */
   int launches_per_op;        /* kernel launches the schedule takes per operation in stream mode (path vector_path) */
-  int streaming;              /* 1: nontemporal loads and stores (operations of >= 1e9 algorithmic bytes) */
+  int streaming;              /* step kernels: 1: nontemporal loads and stores (operations of >= 1e9 algorithmic
+                                 bytes) */
   int xcd_run;                /* step kernels: each XCD takes runs of this many consecutive work items
                                  (0: a contiguous eighth of each step; all-gather 0, reduce-scatter 32) */
   int list_schedule;          /* 1: the list schedule of PAT_AGGREGATION_BUDGET (T = chunks per step) */
@@ -293,6 +294,21 @@ typedef struct {
 
 pat_status_t pat_plan_info(pat_collective_t coll, int nranks, size_t count, pat_dtype_t dtype,
                            pat_plan_info_t* out);
+
+/* What an operation launches at the current settings (execution mode, fusion,
+ * linear order, budget, environment, a trace of the schedule that is armed):
+ * the decision the entry points make, for a plan that is made now.  For
+ * pat_reducescatter_noalloc: in stream mode.  Host-only: needs no GPU. */
+typedef struct {
+  int walk;        /* 1: one walk launch; 0: the step schedule's launches (or nothing) */
+  int launches;    /* kernels per operation (graph mode: in its graph); 0: none (one rank, an empty chunk).
+                      A walk of more than 2^31 lanes counts as one, whatever grids it takes. */
+  int nontemporal; /* 1: nontemporal accesses (walked reduce-scatters of >= 1e8 bytes of send buffers; walked
+                      all-gathers: the stores; else pat_plan_info's streaming) */
+} pat_launch_info_t;
+
+pat_status_t pat_launch_info(pat_collective_t coll, int nranks, size_t count, pat_dtype_t dtype,
+                             pat_launch_info_t* out);
 
 /*
  * Step table of a plan (one piece), host-only.  For step s (in execution

@@ -75,6 +75,12 @@ bool pipeline_now() {
   return e && e[0] == '1';
 }
 
+// Step clock: plans made while PAT_STEP_CLOCK is 1 record their fused launches' steps.
+bool step_clock_now() {
+  const char* e = std::getenv("PAT_STEP_CLOCK");
+  return e && e[0] == '1';
+}
+
 int fusion_now() {
   if (g_fusion >= 0) return g_fusion;
   if (const char* e = std::getenv("PAT_TOP_FUSION")) {
@@ -500,7 +506,7 @@ pat_status_t create_plan(int coll, int N, int64_t count, pat_dtype_t dt, size_t 
   HIP_TRY(hipHostMalloc((void**)&p->pinned, Plan::kStages * 2 * size_t(N) * sizeof(void*), hipHostMallocDefault));
   for (hipEvent_t& e : p->upload_done) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   HIP_TRY(hipEventCreateWithFlags(&p->done, hipEventDisableTiming));
-  if (const char* e = std::getenv("PAT_STEP_CLOCK")) p->step_clock = e[0] == '1';
+  p->step_clock = step_clock_now();
   if (const char* e = std::getenv("PAT_DEBUG")) {
     if (e[0] == '1') {
       std::fprintf(stderr,
@@ -811,29 +817,41 @@ constexpr double kWalkStreamingBytes = 1e8;
 // adds in no other, and that one does not depend on the budget, the pieces or
 // the aggregation rule) of sizes a walk is the faster one for, and nothing
 // that asks for the schedule's own launches.
-bool walk_applies(const HostPlan& h) {
-  const pat::PlanDesc& d = h.desc;
+bool walk_applies(const pat::PlanDesc& d) {
   if (d.coll == 1 &&
       (d.order != pat::kFarFirst || d.count < pat::kWalkLeastElems || d.N > pat::kWalkMostRanks))
     return false;
   return !d.pipelined && fusion_now() == PAT_FUSION_AUTO && !step_schedule_asked();
 }
 
+// The same for an operation of the plan cache's entry points in execution mode
+// `mode`, with a plan that has a step clock or none.
+bool runs_as_walk(const pat::PlanDesc& d, int mode, bool step_clock) {
+  return mode == PAT_EXEC_STREAM && !g_trace.steps && !step_clock && walk_applies(d);
+}
+
+// Bytes of all send buffers of a reduce-scatter, of all receive buffers of an
+// all-gather.
+double large_side_bytes(const pat::PlanDesc& d) { return double(d.N) * d.N * double(d.count) * d.esize_in; }
+
+// Whether a walk's accesses are nontemporal (an all-gather's stores always are).
+bool walk_streams(const pat::PlanDesc& d) { return d.coll == 0 || large_side_bytes(d) >= kWalkStreamingBytes; }
+
 hipError_t enqueue_walk(const HostPlan& h, pat_dtype_t dt, int vi, const pat::KCtx& cx, const pat::WalkRows& rows,
                         hipStream_t q, Trace* trace = nullptr) {
   const pat::PlanDesc& d = h.desc;
-  const double chunk = double(d.count) * d.esize_in, input = double(d.N) * d.N * chunk;
   const bool traced = trace && trace->used < trace->max;
   if (traced) {
     const hipError_t e = hipEventRecord(trace->ev[2 * trace->used], q);
     if (e != hipSuccess) return e;
   }
-  hipError_t e = pat::launch_walk(variant_for(d.coll, dt, vi), input >= kWalkStreamingBytes, cx, rows, q);
+  hipError_t e = pat::launch_walk(variant_for(d.coll, dt, vi), walk_streams(d), cx, rows, q);
   if (e != hipSuccess || !traced) return e;
   const int j = trace->used;
   e = hipEventRecord(trace->ev[2 * j + 1], q);
   if (e != hipSuccess) return e;
-  trace->bytes[j] = input + d.N * chunk;  // each input read once, each output written once
+  // each input read once, each output written once
+  trace->bytes[j] = large_side_bytes(d) + double(d.N) * double(d.count) * d.esize_in;
   trace->kind[j] = 2;
   trace->step[j] = 0;
   trace->used = j + 1;
@@ -945,7 +963,7 @@ pat_status_t run(int coll, const void* const* send, void* const* recv, size_t co
 
   const int mode = mode_now();
   const pat::WalkRows rows = pat::walk_rows(send, recv, N);
-  const bool walk = mode == PAT_EXEC_STREAM && !g_trace.steps && !plan->step_clock && walk_applies(h);
+  const bool walk = runs_as_walk(h.desc, mode, plan->step_clock);
   // A walk whose launch carries the buffers' addresses uses nothing of the
   // plan's device memory.
   const bool on_device = !walk || rows.table;
@@ -1162,7 +1180,7 @@ pat_status_t run_noalloc(int coll, const void* const* send, void* const* recv, s
   }
   const HostPlan& h = ss.plan;
   const int vi = path_for(h, vec);
-  const bool walk = walk_applies(h);
+  const bool walk = walk_applies(h.desc);
   const pat::WalkRows rows = pat::walk_rows(send, recv, N);
   if (!walk && ss.vi != vi) {  // a walk reads the pointer tables at most
     ss.vi = -1;
@@ -1346,6 +1364,28 @@ pat_status_t pat_plan_info(pat_collective_t coll, int nranks, size_t count, pat_
   info.xcd_run = (int)std::min<int64_t>(xcd_run_for((int)coll), INT32_MAX);
   info.list_schedule = d.sched.list ? 1 : 0;
   *out = info;
+  return PAT_OK;
+}
+
+pat_status_t pat_launch_info(pat_collective_t coll, int nranks, size_t count, pat_dtype_t dtype,
+                             pat_launch_info_t* out) {
+  if (!out) return PAT_ERR_INVALID_ARGUMENT;
+  pat_plan_info_t info;
+  pat_status_t s = pat_plan_info(coll, nranks, count, dtype, &info);
+  if (s != PAT_OK) return s;
+  pat::PlanDesc d;
+  if ((s = describe((int)coll, nranks, count, dtype, &d)) != PAT_OK) return s;
+  pat_launch_info_t li{};
+  if (nranks > 1 && count > 0) {
+    std::lock_guard<std::mutex> lock(g_mu);
+    const int mode = mode_now();
+    li.walk = runs_as_walk(d, mode, step_clock_now()) ? 1 : 0;
+    li.launches = li.walk || mode == PAT_EXEC_PERSISTENT ? 1
+                  : mode == PAT_EXEC_DATAFLOW            ? info.pieces
+                                                         : info.launches_per_op;
+    li.nontemporal = li.walk ? walk_streams(d) : info.streaming;
+  }
+  *out = li;
   return PAT_OK;
 }
 

@@ -63,7 +63,7 @@ EXPORTS = (
     "pat_allgather", "pat_reducescatter", "pat_reducescatter_noalloc", "pat_set_buffer_bytes", "pat_get_buffer_bytes",
     "pat_set_exec_mode", "pat_get_exec_mode", "pat_set_linear_order", "pat_get_linear_order",
     "pat_set_top_fusion", "pat_get_top_fusion", "pat_set_aggregation", "pat_get_aggregation",
-    "pat_set_barrier_timeout_us", "pat_plan_info",
+    "pat_set_barrier_timeout_us", "pat_plan_info", "pat_launch_info",
     "pat_plan_steps", "pat_trace_start", "pat_trace_start_as_run", "pat_trace_read", "pat_step_clock",
     "pat_cache_stats",
     "pat_check_device_status", "pat_last_hip_error", "pat_status_string",
@@ -83,6 +83,13 @@ class pat_plan_info_t(ctypes.Structure):
         ("launches_per_op", ctypes.c_int), ("streaming", ctypes.c_int), ("xcd_run", ctypes.c_int),
         ("list_schedule", ctypes.c_int),
     ]
+
+    def as_dict(self):
+        return {name: getattr(self, name) for name, _ in self._fields_}
+
+
+class pat_launch_info_t(ctypes.Structure):
+    _fields_ = [("walk", ctypes.c_int), ("launches", ctypes.c_int), ("nontemporal", ctypes.c_int)]
 
     def as_dict(self):
         return {name: getattr(self, name) for name, _ in self._fields_}
@@ -125,6 +132,8 @@ def lib():
             "pat_set_barrier_timeout_us": ([ctypes.c_uint32], ctypes.c_int),
             "pat_plan_info": ([ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int,
                                ctypes.POINTER(pat_plan_info_t)], ctypes.c_int),
+            "pat_launch_info": ([ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int,
+                                 ctypes.POINTER(pat_launch_info_t)], ctypes.c_int),
             "pat_plan_steps": ([ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int, _I32P, _I32P,
                                 ctypes.c_int, _I32P, _I32P, _I32P, _I32P, ctypes.c_int,
                                 ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)], ctypes.c_int),
@@ -337,6 +346,13 @@ def pat_plan_info(coll, nranks, count, dtype):
     """Returns (status, dict)."""
     info = pat_plan_info_t()
     st = lib().pat_plan_info(int(coll), int(nranks), int(count), _dtype(dtype), ctypes.byref(info))
+    return st, info.as_dict()
+
+
+def pat_launch_info(coll, nranks, count, dtype):
+    """Returns (status, dict): what the operation launches at the current settings."""
+    info = pat_launch_info_t()
+    st = lib().pat_launch_info(int(coll), int(nranks), int(count), _dtype(dtype), ctypes.byref(info))
     return st, info.as_dict()
 
 

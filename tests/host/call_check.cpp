@@ -44,7 +44,7 @@ static pat_status_t call(int coll, const Buffers& b, size_t count, pat_dtype_t d
 static void check_no_environment() {
   EXPECT(clearenv() == 0 && environ == nullptr);
   for (int coll = 0; coll < 2; ++coll) {
-    fake::launches.clear();
+    fake::forget();
     EXPECT(call(coll, buffers(coll, 6, 4096), 1024, PAT_FLOAT32) == PAT_OK);
     EXPECT(fake::launches.size() == 1 && fake::launches[0].kind == 'w');
   }
@@ -63,7 +63,7 @@ static void check_trace() {
     EXPECT(pat_plan_info((pat_collective_t)coll, n, count, PAT_FLOAT32, &info) == PAT_OK);
     for (bool steps : {false, true}) {
       EXPECT((steps ? pat_trace_start(100) : pat_trace_start_as_run(100)) == PAT_OK);
-      fake::launches.clear();
+      fake::forget();
       EXPECT(call(coll, b, count, PAT_FLOAT32) == PAT_OK && call(coll, b, count, PAT_FLOAT32) == PAT_OK);
       float ms[100];
       double bytes[100];
@@ -80,7 +80,7 @@ static void check_trace() {
       EXPECT(steps ? std::abs(sum / 2 / info.alg_bytes - 1) < 1e-9 : sum == 2 * needed);
       EXPECT(pat_trace_read(ms, bytes, kind, step, 100, &used) == PAT_ERR_INVALID_ARGUMENT);  // disarmed
     }
-    fake::launches.clear();
+    fake::forget();
     EXPECT(call(coll, b, count, PAT_FLOAT32) == PAT_OK);
     EXPECT(fake::launches.size() == 1 && fake::launches[0].kind == 'w');
     EXPECT(pat_trace_start_as_run(1) == PAT_OK);  // room for one launch: the second call records nothing
@@ -91,10 +91,79 @@ static void check_trace() {
   EXPECT(pat_trace_start_as_run(0) == PAT_ERR_INVALID_ARGUMENT);
 }
 
+// pat_launch_info says what a call launches, on both sides of every limit of
+// the choice, in every mode (a graph's capture aside) and at every setting
+// that it depends on.
+static void check_routes() {
+  struct Case {
+    int coll, n;
+    size_t count;
+    pat_dtype_t dt;
+    bool walk;  // at the default settings
+  };
+  const Case cases[] = {
+      {1, 6, 15, PAT_FLOAT32, false},   {1, 6, 16, PAT_FLOAT32, true},      {1, 6, 16, PAT_BFLOAT16, true},
+      {1, 6, 15, PAT_INT32, false},     {1, 4096, 16, PAT_BFLOAT16, true},  {1, 4097, 16, PAT_BFLOAT16, false},
+      {1, 2, 16, PAT_FLOAT32, true},    {0, 2, 1, PAT_BFLOAT16, true},      {0, 5000, 3, PAT_FLOAT32, true},
+      {1, 70, 5098, PAT_FLOAT32, true}, {1, 70, 5103, PAT_FLOAT32, true},  // 0.999e8 and 1.0002e8 bytes
+      {1, 64, 262144, PAT_FLOAT32, true}, {0, 64, 262144, PAT_FLOAT32, true}, {1, 1, 64, PAT_FLOAT32, false},
+  };
+  auto agrees = [](const Case& c, bool walk) {
+    pat_launch_info_t li;
+    EXPECT(pat_launch_info((pat_collective_t)c.coll, c.n, c.count, c.dt, &li) == PAT_OK);
+    fake::forget();
+    EXPECT(call(c.coll, buffers(c.coll, c.n, c.count * (c.dt == PAT_BFLOAT16 ? 2 : 4)), c.count, c.dt) == PAT_OK);
+    EXPECT((li.walk == 1) == walk);
+    EXPECT(li.launches == (int)fake::launches.size());
+    for (const auto& l : fake::launches) EXPECT((l.kind == 'w') == walk && l.streaming == (li.nontemporal == 1));
+  };
+  for (const Case& c : cases) {
+    agrees(c, c.walk);
+    if (c.n > 1000) continue;  // the settings: at small plans
+    for (int mode : {PAT_EXEC_PERSISTENT, PAT_EXEC_DATAFLOW}) {
+      EXPECT(pat_set_exec_mode(mode) == PAT_OK);
+      agrees(c, false);
+    }
+    EXPECT(pat_set_exec_mode(PAT_EXEC_STREAM) == PAT_OK);
+    for (int fusion : {PAT_FUSION_OFF, PAT_FUSION_ON}) {
+      EXPECT(pat_set_top_fusion(fusion) == PAT_OK);
+      agrees(c, false);
+    }
+    EXPECT(pat_set_top_fusion(PAT_FUSION_AUTO) == PAT_OK);
+    EXPECT(pat_set_linear_order(PAT_LINEAR_CLOSE_FIRST) == PAT_OK);
+    agrees(c, c.walk && c.coll == 0);
+    EXPECT(pat_set_linear_order(PAT_LINEAR_FAR_FIRST) == PAT_OK);
+    EXPECT(pat_set_buffer_bytes(1024) == PAT_OK);  // pieces: no part of a walk
+    agrees(c, c.walk);
+    EXPECT(pat_set_buffer_bytes(0) == PAT_OK);
+    EXPECT(pat_trace_start(1) == PAT_OK);
+    agrees(c, false);
+    EXPECT(pat_trace_start_as_run(1) == PAT_OK);
+    agrees(c, c.walk);
+    int used = 0;
+    EXPECT(pat_trace_read(nullptr, nullptr, nullptr, nullptr, 1, &used) == PAT_OK && used == (c.n > 1));
+    for (const char* name : {"PAT_WALK", "PAT_TREE_TILE", "PAT_TREE_FUSE_VECS", "PAT_TREE_FUSE_BYTES",
+                             "PAT_TREE_EDGE_CACHE", "PAT_STREAMING", "PAT_STEP_CLOCK"}) {
+      EXPECT(pat_finalize() == PAT_OK);  // the step clock is a plan's
+      setenv(name, std::strcmp(name, "PAT_STEP_CLOCK") ? "0" : "1", 1);
+      agrees(c, false);
+      unsetenv(name);
+    }
+    EXPECT(pat_finalize() == PAT_OK);
+    setenv("PAT_WALK", "1", 1);
+    agrees(c, c.walk);
+    unsetenv("PAT_WALK");
+  }
+  pat_launch_info_t li;
+  EXPECT(pat_launch_info(PAT_ALLGATHER, 0, 1, PAT_FLOAT32, &li) == PAT_ERR_INVALID_ARGUMENT);
+  EXPECT(pat_launch_info(PAT_ALLGATHER, 2, 1, PAT_FLOAT32, nullptr) == PAT_ERR_INVALID_ARGUMENT);
+}
+
 int main(int argc, char** argv) {
   const std::string which = argc > 1 ? argv[1] : "";
   if (which == "no_environment") check_no_environment();
   else if (which == "trace") check_trace();
+  else if (which == "routes") check_routes();
   else return std::fprintf(stderr, "no check named '%s'\n", which.c_str()), 2;
   EXPECT(pat_finalize() == PAT_OK);
   std::printf("%s: %d failures\n", which.c_str(), failures);

@@ -50,6 +50,10 @@ inline void run_until(uint64_t position) {
   }
 }
 inline void drain() { run_until(queued); }
+inline void forget() {  // the launches so far
+  drain();
+  launches.clear();
+}
 
 inline void launch(char kind, bool streaming, const pat::KCtx& cx, const pat::WalkRows* rows = nullptr) {
   const size_t i = launches.size();
@@ -104,7 +108,8 @@ hipError_t hipMemcpy(void* dst, const void* src, size_t n, hipMemcpyKind) {
   std::memcpy(dst, src, n);
   return hipSuccess;
 }
-hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t) {
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind kind, hipStream_t) {
+  if (kind == hipMemcpyDeviceToDevice) return fake::push([] {}), hipSuccess;  // of user buffers, which do not exist
   auto it = fake::pinned.upper_bound((char*)src);
   if (it != fake::pinned.begin() && (char*)src < std::prev(it)->first + std::prev(it)->second) {
     fake::push([=] { std::memcpy(dst, src, n); });

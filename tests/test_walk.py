@@ -4,8 +4,8 @@ Sizes sit where the launch changes shape: one lane group per vector or several
 (2, 4: 256 lanes; 8, 16: 64 per group), a remainder of a group's positions,
 truncated parts, chunks that fill a workgroup or share one, a partial last
 vector, the smallest chunk and the largest rank count a walk is taken for and
-the first beyond.  Bar: the same bits as the CPU oracle's PAT order, and as the
-step kernels (fusion off) on the same inputs.
+the first beyond; which launch ran is asserted.  Bar: the same bits as the CPU
+oracle's PAT order, and as the step kernels (fusion off) on the same inputs.
 """
 
 import os
@@ -162,12 +162,18 @@ def test_walked_reducescatter(n, count, dtype, layout, entry):
     for fusion in ("auto", "off"):
         for r in recv:
             r.view(torch.uint8).fill_(0xA5)
+        walks = fusion == "auto" and count >= 16 and n <= 4096
         pat.check(pat.pat_set_top_fusion(fusion))
         try:
+            assert pat.pat_launch_info(pat.PAT_REDUCESCATTER, n, count, dtype)[1]["walk"] == walks
+            pat.check(pat.pat_trace_start_as_run(10000))
             pat.check(getattr(pat, "pat_" + entry)(S, R, count, dtype, pat.PAT_SUM, n, stream))
             torch.cuda.synchronize()
+            kinds = [k for _, _, k, _ in pat.pat_trace_read(10000)[1]]
         finally:
             pat.check(pat.pat_set_top_fusion("auto"))
+        if entry == "reducescatter":  # the other one is not traced
+            assert kinds == [2] if walks else kinds and 2 not in kinds
         outs.append(np.stack([bits(r) for r in recv]))
     np.testing.assert_array_equal(outs[0], outs[1])
     want = native.reducescatter(dtype, n, count, dist=DIST[dtype], seed=seed)["pat"]
@@ -302,8 +308,10 @@ def test_walked_allgather(n, count, dtype, layout):
     for r in range(n):
         mark[skew + r * (n * count + gap): skew + r * (n * count + gap) + n * count] = False
     outside = whole[mark].clone()
+    pat.check(pat.pat_trace_start_as_run(10))
     pat.check(pat.pat_allgather(pat.pointer_array(send), pat.pointer_array(recv), count, dtype, n, stream))
     torch.cuda.synchronize()
+    assert [k for _, _, k, _ in pat.pat_trace_read(10)[1]] == [2]  # a walk
     bad = [r for r in range(n) if not torch.equal(recv[r].view(torch.uint8), want.view(torch.uint8))]
     assert not bad, bad[:8]
     assert torch.equal(whole[mark], outside)
