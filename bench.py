@@ -12,11 +12,11 @@ Prints one JSON line:
                 bracketed by its own HIP events (the median is reported too)
 * roofline   -- the dominant kernel's own rate against the 8 TB/s HBM3E peak;
                 traffic from the committed rocprofv3 counter summary when it
-                matches the current kernel source.  An operation that runs as
-                one walk launch: the bytes it cannot do without (each input
-                read once, each output written once) / the operation's time.
-                Else the algorithmic bytes of the kernel's launches / their
-                durations, from the library's launch trace
+                matches the current kernel source.  The bytes of the kernel's
+                launches / their durations, from the library's launch trace of
+                three operations after the timed ones; a walk's bytes are those
+                it cannot do without (each input read once, each output written
+                once), a step's the algorithmic ones
 * step_schedule -- for a walked operation: the same schedule run step by step,
                 three traced operations after the timed ones
 * cpu_baseline -- the CPU oracle timed in the same process: the threaded C++
@@ -74,11 +74,13 @@ KERNEL_SOURCES = {
 }
 
 
-def runs_as_walk(coll, count, mode):
-    """Whether the library runs such an operation as one walk launch (its rule
-    for stream mode at the default settings; this file sets no step-kernel
-    tuning variable outside the sweeps)."""
-    return mode == "stream" and (coll == "ag" or count >= 16) and os.environ.get("PAT_WALK") != "0"
+def launch_info(coll, n, count, dtype):
+    """What the library launches for such an operation at the current settings:
+    {"walk", "launches", "nontemporal"}."""
+    from paper_2506_20252_amd import pat
+    st, info = pat.pat_launch_info(pat.PAT_REDUCESCATTER if coll == "rs" else pat.PAT_ALLGATHER, n, count, dtype)
+    pat.check(st)
+    return info
 
 
 def needed_bytes(coll, n, count, dtype):
@@ -123,9 +125,9 @@ def kernel_source_hash(family="step"):
 
 
 def committed_traffic(workload_id, mode, kernel):
-    """HBM-side bytes per launch of `kernel` (step_kernel / tree_kernel / a walk kernel) from
-    the committed counter summary, if it was taken on the current kernel
-    source; else None.  Stream and graph modes launch the same kernels; the
+    """HBM-side bytes per launch of `kernel` (step_kernel / tree_kernel / a walk
+    kernel) from the committed counter summary, if it was taken on the current
+    kernel source; else None.  Stream and graph modes launch the same kernels; the
     persistent kernel has no summary."""
     if mode == "persistent":
         return None
@@ -262,8 +264,8 @@ def small_size_latency(reps=200):
         out[f"{coll}_us"] = round(mean_ms * 1e3, 2)
         out[f"{coll}_median_us"] = round(statistics.median(per) * 1e3, 2)
         out["steps"] = info["steps"]
-        walked = runs_as_walk("rs" if coll == "reducescatter" else "ag", count, "stream")
-        out[f"{coll}_launches"] = 1 if walked else info["launches_per_op"]
+        launched = launch_info("rs" if coll == "reducescatter" else "ag", n, count, "float32")
+        out[f"{coll}_launches"] = launched["launches"]
         del send, recv, S, R
     torch.cuda.empty_cache()
     return out
@@ -313,10 +315,9 @@ def other_workloads(reps=50):
         pat.check(pat.pat_check_device_status(stream))
         sec = mean_ms / 1e3
         st, info = pat.pat_plan_info(code, n, count, dtype)
-        walked = runs_as_walk(coll, count, "stream")
         rows.append({"workload": desc, "us": round(sec * 1e6, 2), "median_us": round(statistics.median(per) * 1e3, 2),
                      "steps": info["steps"],
-                     "launches": 1 if walked else info["launches_per_op"],
+                     "launches": launch_info(coll, n, count, dtype)["launches"],
                      "bus_gbps": round(n * info["bus_bytes_per_rank"] / sec / 1e9, 2),
                      "hbm_frac": round(needed_bytes(coll, n, count, dtype) / sec / 1e9 / HBM_PEAK_GBPS, 4)})
         del send, recv, S, R
@@ -602,7 +603,7 @@ def size_sweep(n=128, max_input_bytes=16 << 30, reps_bytes=32 << 30):
             sec = e0.elapsed_time(e1) / 1e3 / reps
             rows.append({"collective": "reduce-scatter" if coll == "rs" else "all-gather", "chunk_bytes": count * 4,
                          "T": info["T"], "steps": info["steps"],
-                         "launches": 1 if runs_as_walk(coll, count, "stream") else info["launches_per_op"],
+                         "launches": launch_info(coll, n, count, "float32")["launches"],
                          "us": round(sec * 1e6, 2),
                          "bus_gbps": round(n * info["bus_bytes_per_rank"] / sec / 1e9, 1),
                          "hbm_frac": round(needed_bytes(coll, n, count, "float32") / sec / 1e9 / HBM_PEAK_GBPS, 4)})
@@ -690,7 +691,10 @@ def time_pair_and_reps(op, stream, reps):
 
 
 def kernel_name(coll, dtype, path, streaming, kind):
-    """The kernel template a launch runs (as rocprofv3 names it, abridged)."""
+    """The kernel template a launch runs (as rocprofv3 names it, abridged; a
+    walk over the rows of one tensor, which is how this file holds buffers)."""
+    if kind == 2:
+        return {"rs": "walk_rs_kernel", "ag": "walk_ag_rows_kernel"}[coll]
     if coll == "rs":
         traits = {"int32": "TI32", "float32": "TF32", "bfloat16": "TB16"}[dtype] + {0: "S", 1: "V", 2: "U"}[path]
         op = f"RsOp<{traits}, {'true' if streaming else 'false'}>"
@@ -700,14 +704,15 @@ def kernel_name(coll, dtype, path, streaming, kind):
     return ("tree_kernel<" if kind == 1 else "step_kernel<") + op + ">"
 
 
-def kernel_roofline(info, coll, dtype, reps):
+def kernel_roofline(info, coll, dtype, reps, walked=False):
     """The launch trace of `reps` operations: a HIP event pair around every
     kernel launch, recorded by the library on the kernels' stream (armed before
     the operations), and each launch's algorithmic bytes from the plan's byte
-    model.  The dominant kernel is the one with the most traced
-    time; its rate is its launches' bytes over their summed durations."""
+    model (a walk's: the bytes it needs).  The dominant kernel is the one with
+    the most traced time; its rate is its launches' bytes over their summed
+    durations."""
     from paper_2506_20252_amd import pat
-    launches = info["launches_per_op"]
+    launches = 1 if walked else info["launches_per_op"]
     st, rows = pat.pat_trace_read(reps * launches)
     pat.check(st, "pat_trace_read")
     if len(rows) != reps * launches:
@@ -720,8 +725,9 @@ def kernel_roofline(info, coll, dtype, reps):
         g["launches"] += 1
         g["rates"].append(nbytes / (ms / 1e3) / 1e9 if ms > 0 else 0.0)
     op_bytes = sum(r[1] for r in rows) / reps
-    if abs(op_bytes - info["alg_bytes"]) > 1e-6 * info["alg_bytes"]:
-        raise RuntimeError(f"trace bytes per operation {op_bytes} != plan {info['alg_bytes']}")
+    want = needed_bytes(coll, info["nranks"], info["count"], dtype) if walked else info["alg_bytes"]
+    if abs(op_bytes - want) > 1e-6 * want:
+        raise RuntimeError(f"trace bytes per operation {op_bytes}, expected {want}")
     dom = max(by, key=lambda k: by[k]["ms"])
     g = by[dom]
     achieved = g["bytes"] / (g["ms"] / 1e3) / 1e9
@@ -905,10 +911,19 @@ def main():
     pat.check(pat.pat_check_device_status(stream))
     sec = ms / 1e3
     bus_per_rank = info["bus_bytes_per_rank"]
-    # The launch trace measures the step schedule, launch by launch, after the
-    # timed operations: a traced operation runs its steps, and the event pairs
-    # slow it by a few microseconds per launch.  One untraced operation first
-    # loads the step kernels.
+    # The launch traces measure single launches, after the timed operations
+    # (the event pairs slow an operation by a few microseconds per launch):
+    # first of what the timed operations launched, if that was a walk, then of
+    # the step schedule.  One untraced operation first loads the step kernels.
+    launched = launch_info(coll, n, count, dtype)
+    walked = bool(launched["walk"])
+    if walked:
+        traced = min(args.steps, 3)
+        pat.check(pat.pat_trace_start_as_run(traced))
+        for _ in range(traced):
+            pat.check(op(), "traced")
+        torch.cuda.synchronize()
+        roof = kernel_roofline(info, coll, dtype, traced, walked=True)
     step_roof = None
     if args.mode == "stream":
         asked = os.environ.get("PAT_WALK")
@@ -921,17 +936,11 @@ def main():
             pat.check(op(), "traced")
         torch.cuda.synchronize()
         step_roof = kernel_roofline(info, coll, dtype, traced)
-    walked = runs_as_walk(coll, count, args.mode)
-    if walked:
-        need = needed_bytes(coll, n, count, dtype)
-        roof = {"kernel": f"walk_{coll}_kernel", "achieved": need / sec / 1e9, "launches_per_op": 1,
-                "avg_launch_us": round(ms * 1e3, 3), "bytes_per_launch": need,
-                "timing": "HIP events around the timed operations, one launch each"}
-    elif args.mode == "stream":
-        roof = step_roof
+        if not walked:
+            roof = step_roof
     else:
         # no per-launch trace in these modes: the operation's time spread over its launches
-        launches = 1 if args.mode == "persistent" else info["launches_per_op"]
+        launches = launched["launches"]
         roof = {"kernel": "persistent_kernel" if args.mode == "persistent" else "step_kernel",
                 "achieved": info["alg_bytes"] / launches / (sec / launches) / 1e9, "launches_per_op": launches,
                 "timing": "operation time / launches (no per-launch trace in this mode)"}
@@ -942,6 +951,10 @@ def main():
         # itself was (below `frac` where the kernel hits in cache)
         roof["traffic_frac"] = round(traffic / (roof["avg_launch_us"] * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4)
 
+    # Settings that shape the step schedule's launches, and no walk's.
+    schedule = {"buffer_bytes_per_slot": pat.pat_get_buffer_bytes(), "T": info["T"], "pat_steps": info["steps"],
+                "pieces": info["pieces"], "fused_steps": 0 if args.mode == "persistent" else info["fused_steps"],
+                "streaming_accesses": bool(info["streaming"]), "xcd_run": info["xcd_run"]}
     out = {
         "metric": METRIC,
         "value": round(n * bus_per_rank / sec / 1e9, 3),
@@ -959,11 +972,8 @@ def main():
         "data": "synthetic",
         "config": {"workload": desc, "nranks": n, "count": count, "input_dtype": dtype,
                    "collective": "reduce-scatter" if coll == "rs" else "all-gather", "exec_mode": args.mode,
-                   "buffer_bytes_per_slot": pat.pat_get_buffer_bytes(), "T": info["T"],
-                   "pat_steps": info["steps"], "pieces": info["pieces"],
-                   "walk": walked, "fused_steps": 0 if args.mode == "persistent" else info["fused_steps"],
-                   "streaming_accesses": bool(info["streaming"]), "xcd_run": info["xcd_run"],
-                   "seed": seed},
+                   "walk": walked, "launches": launched["launches"],
+                   "nontemporal": bool(launched["nontemporal"]), **({} if walked else schedule), "seed": seed},
         "bus_gbps_per_rank": round(bus_per_rank / sec / 1e9, 4),
         "latency_us": round(ms * 1e3, 2),
         "schedule_bytes_per_op": info["alg_bytes"],
@@ -972,7 +982,7 @@ def main():
                      "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic, **roof},
     }
     if walked:
-        out["step_schedule"] = {**step_roof, "achieved": round(step_roof["achieved"], 2),
+        out["step_schedule"] = {**schedule, **step_roof, "achieved": round(step_roof["achieved"], 2),
                                 "frac": round(step_roof["achieved"] / HBM_PEAK_GBPS, 4)}
     if not args.no_latency:
         out["small_size_latency"] = small_size_latency()
