@@ -276,16 +276,12 @@ __global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkArgs<WalkCtx, SPACED>
     v = (int64_t)(blk - (uint32_t)R * cx.tiles) * lanes + lane;
     live = v < cx.V;
   } else {
-    const int64_t f = (int64_t)blk * lanes + lane;
-    const int64_t vecs = cx.N * cx.V;
-    live = f < vecs;
-    if (vecs < (int64_t(1) << 31)) {
-      R = (int)((uint32_t)f / (uint32_t)cx.V);
-      v = (uint32_t)f - (uint32_t)R * (uint32_t)cx.V;
-    } else {
-      R = (int)(f / cx.V);
-      v = f - (int64_t)R * cx.V;
-    }
+    // Chunks share workgroups only below 8 * lanes <= 2048 vectors, and there
+    // are at most kWalkMostRanks: 32 bits hold every index.
+    const uint32_t f = blk * (uint32_t)lanes + (uint32_t)lane;
+    live = f < (uint32_t)cx.N * (uint32_t)cx.V;
+    R = (int)(f / (uint32_t)cx.V);
+    v = f - (uint32_t)R * (uint32_t)cx.V;
   }
   const bool part = cx.back && v == cx.V - 1;
   const int64_t voff = v * (int64_t)sizeof(in_t) - (part ? cx.back * T::kElem : 0);
