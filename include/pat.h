@@ -23,20 +23,24 @@
  *   - Status codes only; nothing is thrown across this boundary.
  *   - `sendbufs` / `recvbufs` are HOST arrays of `nranks` DEVICE pointers,
  *     read during the call only (the library copies them into a device
- *     table it owns, or passes them with the kernel launch).  The buffers themselves are owned by the caller and
- *     must stay valid until `stream` has finished the operation.
+ *     table it owns, or passes them with the kernel launch).  The buffers
+ *     themselves are owned by the caller and must stay valid until `stream`
+ *     has finished the operation.
  *   - Calls are asynchronous with respect to the host and ordered on
  *     `stream`.  Calls that use the same (operation, nranks, count, dtype,
  *     buffer budget) share library-owned intermediate buffers: they must be
  *     ordered on one stream (or otherwise serialised by the caller).
- *   - Pointers must be aligned to the element size.  When every pointer is
- *     16-byte aligned and count * sizeof(element) is a multiple of 16, the
- *     kernels move 128-bit vectors.  Otherwise they still move 128-bit
- *     vectors, at element-aligned addresses, as long as every piece of a
- *     chunk holds at least one (16 bytes; bf16 reduce-scatter: 4 elements):
- *     a piece's last, partial vector is moved back to end where the piece
- *     ends and stores only its own elements.  Pieces under one vector move
- *     single elements (correct, slower).
+ *   - Pointers must be aligned to the element size; nothing more is needed
+ *     for full-width accesses.  A walk launch (see pat_set_top_fusion) reads
+ *     and writes vectors at any element alignment, 16 bytes (bf16
+ *     reduce-scatter: 4 elements, 8 bytes); a reduce-scatter chunk's last,
+ *     partial vector is moved back to end where the chunk ends and stores only
+ *     its own elements, and an all-gather's vectors across chunks move element
+ *     by element.  The step kernels take aligned vectors when every pointer is
+ *     16-byte aligned and count * sizeof(element) is a multiple of 16, else
+ *     vectors at element-aligned addresses with such a last vector per piece
+ *     of a chunk, as long as every piece holds at least one, else single
+ *     elements (correct, slower).
  *   - In place is allowed only in the MPI/NCCL form given per operation;
  *     any other overlap between a receive buffer and another buffer is
  *     PAT_ERR_INVALID_ARGUMENT.  Send buffers may overlap each other.
@@ -161,7 +165,8 @@ pat_status_t pat_reducescatter(const void* const* sendbufs, void* const* recvbuf
  *
  * Errors: as pat_reducescatter, plus PAT_ERR_TOO_LARGE (nothing is launched)
  * when the plan's slots (slot_bytes_total of pat_plan_info) and tables
- * exceed the array.
+ * exceed the array, also where the call would run as a walk, which uses no
+ * more of it than the pointer tables.
  */
 #define PAT_NOALLOC_SCRATCH_BYTES ((size_t)256 << 20)
 pat_status_t pat_reducescatter_noalloc(const void* const* sendbufs, void* const* recvbufs, size_t count,
@@ -230,22 +235,24 @@ int pat_get_exec_mode(void);
  * environment variable: auto | on | off) fuses the far end of the fusable
  * range, the steps that move at most 128 MiB and in which one tree's edges
  * over one tile of its chunk amount to at most 2048 vectors, when there are
- * two or more such steps; ON
- * fuses the whole fusable range whenever it has two or more steps.  Neither
- * fuses a chunk that is split into pieces.  A tile is the smallest power of
- * two from 32 to 256 vectors that keeps the launch within 1024 workgroups.
+ * two or more such steps; ON fuses the whole fusable range whenever it has two
+ * or more steps.  Neither fuses a chunk that is split into pieces.  A tile is
+ * the smallest power of two from 32 to 256 vectors that keeps the launch within
+ * 1024 workgroups.
  *
  * AUTO in stream mode goes further: an operation runs as one walk launch, in
  * which no intermediate buffer is in memory.  A far-first reduce-scatter of at
  * most 4096 ranks and at least 16 elements per chunk: each lane walks the whole
- * tree (or an aligned part of it) of one 16-byte vector in the linear order of
+ * tree (or an aligned part of it) of one 4-element vector in the linear order of
  * section "The PAT algorithm", so that the one chunk per distance the linear
  * walk needs to hold is a register, and each input is read once.  An all-gather
  * (either linear order): each lane reads one vector of the concatenation once
  * and stores it to several ranks, as every node of a chunk's tree forwards the
  * bytes it received.  Results and the summation order are the same; the buffer
  * budget, pieces and the aggregation rule, which shape the step schedule, do
- * not change a walk.  The step schedule runs instead while a trace of it is
+ * not change a walk.  Plans hold the schedule's intermediate buffers also where
+ * every call walks (a setting may change from one call to the next), so what a
+ * plan takes of device memory is what the budget says.  The step schedule runs instead while a trace of it is
  * armed (pat_trace_start), for plans with a step clock, and when the environment
  * has PAT_WALK=0 or one of the step kernels' tuning variables (PAT_TREE_*,
  * PAT_XCD_GRAIN, PAT_STREAMING, PAT_PIECE_PIPELINE).

@@ -247,9 +247,11 @@ __device__ __forceinline__ typename T::acc_t group_sum(const typename T::in_t (&
 // vectors belong to one chunk, whose senders' addresses are then scalar; else
 // they are consecutive vectors of consecutive chunks.
 //
-// A lane reads G positions at a time and has the next G on the way while it
-// adds.  The bound is HBM's read rate.  Measured on MI355X, step schedule ->
-// walk: N=64 float32 1 MiB 1992 -> 650 us, N=128 bf16 4 MiB 52.6 -> 10.8 ms
+// A lane reads G positions at a time and asks for the next G before it adds.
+// Where those loads have a condition (a last group may be partial) the compiler
+// waits for all in flight before it adds: other waves, not the lane's own next
+// loads, cover most of the latency.  The bound of a large operation is HBM's
+// read rate.  Measured on MI355X, step schedule -> walk: N=64 float32 1 MiB 1992 -> 650 us, N=128 bf16 4 MiB 52.6 -> 10.8 ms
 // (6.6 and 6.4 TB/s of input), N=1000 float32 256 B 139 -> 42 us a call.
 //
 // KEYED (power-of-two parts only): a workgroup reads its groups of positions in
@@ -409,8 +411,9 @@ constexpr int walk_slots(int S) {
   return S <= 4 ? 6 : 8;
 }
 // Positions read at a time.  A whole tree: 4.  A part of one: float32 and
-// int32 2 (56 VGPRs with a chunk's own workgroups, 8 waves per SIMD), bf16 4
-// (64 VGPRs).
+// int32 2, bf16 4.  VGPRs of a part's kernels, with a chunk's own workgroups /
+// shared ones: float32 56 / 62-70 at 256 lanes, 64 / 70-78 at 1024; bf16 66 /
+// 74-82 and 74 / 79-90 (64 leave 8 waves per SIMD, 72 7, 80 6, 96 5).
 template <class T>
 constexpr int walk_group(int S) {
   return S == 1 || T::kElem == 2 ? 4 : 2;
@@ -419,8 +422,8 @@ constexpr int walk_group(int S) {
 // S: lane groups per vector.  One reads a whole tree where that alone gives
 // enough waves: walk_waves, about what keeps HBM busy.  Fewer leave it waiting,
 // more cost an LDS exchange per vector and shorter walks.  A group keeps at
-// least kWalkSpan positions (two rounds of loads), and at most what its slots
-// hold.  Measured on MI355X, us at S = 1, 2, 4, 8, 16 (waves at S = 1):
+// least kWalkSpan positions (two to four rounds of loads), and at most what its
+// slots hold.  Measured on MI355X, us at S = 1, 2, 4, 8, 16 (waves at S = 1):
 //   float32  N=50 20 KB (976) 17, 14, 10.5, 10.5, 12; N=500 1200 B (585) -, -,
 //            61, 56, 64; N=100 40 KB (3906) 68, 65, 64, 69, 75; N=10 1 MiB
 //            (10240) 21, 24, 26, 37, 60
@@ -529,9 +532,11 @@ constexpr int kGatherTile = kGatherThreads * 16;  // bytes
 // bytes from its row's start.  Vectors that hold bytes of several chunks, and
 // the row's ends, are read and where necessary stored element by element.
 // ES: bytes per element.
-// Measured on MI355X, step schedule -> walk, a call: N=128 float32 1 MiB 7062 ->
-// 2940 us, N=1000 float32 252 B 148 -> 38 us, N=13 bf16 2002 B in place 23 -> 4.5
-// us.
+// Measured on MI355X, step schedule -> walk, a call, in place: N=128 float32 1
+// MiB 6982 -> 2762 us, N=1000 float32 252 B 134 -> 39 us, N=13 bf16 2002 B 11.6 ->
+// 4.5 us; rows in shuffled order: 7149 -> 2818, 137 -> 58, 11.5 -> 4.4 us.  (The
+// timings above and at the launch are of one tensor's rows through this kernel,
+// which have one of their own below, where they do not say in place.)
 template <int ES, bool SPACED>
 __global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(WalkArgs<GatherCtx, SPACED> args) {
   const GatherCtx& cx = args.cx;
@@ -624,8 +629,10 @@ hipError_t launch_walk_ag(GatherCtx cx, const WalkRows& rows, int esize, hipStre
   if (blocks > (int64_t(1) << 31)) return hipErrorInvalidValue;
   cx.tiles = (uint32_t)tiles;
   // Order: tiles of the same receivers follow each other.  Runs of them per
-  // XCD for large operations only (N=128 float32 1 MiB, 1.05 M blocks: 2967 us
-  // one by one, 2880 us with runs of 256; N=300 4 KiB, 22500: 56 and 64 us).
+  // XCD for large operations only (in place, one by one / runs of 256: N=128
+  // float32 1 MiB, 1.05 M blocks, 3080 / 2760 us; N=50 float32 400 KB 163 / 162
+  // us; N=300 float32 4 KiB, 22500 blocks, 51 / 65 us; but N=700 bf16 32 KiB
+  // 2530 / 2630 us).
   cx.blocks = {(uint32_t)blocks, blocks >= (1 << 18) ? 256u : 1u, 0};
   if (rows.spaced)
     launch_kernel(esize == 2 ? walk_ag_kernel<2, true> : walk_ag_kernel<4, true>, kGatherThreads, cx, rows, stream);
