@@ -38,6 +38,22 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
+def set_mode(mode):
+    """An execution mode of the library, or "steps": stream mode with the step
+    schedule's launches (PAT_WALK=0) where "stream" runs one walk."""
+    if mode == "steps":
+        os.environ["PAT_WALK"] = "0"
+    else:
+        os.environ.pop("PAT_WALK", None)
+    pat.check(pat.pat_set_exec_mode("stream" if mode == "steps" else mode))
+
+
+@pytest.fixture(autouse=True)
+def default_path():
+    yield
+    os.environ.pop("PAT_WALK", None)
+
+
 @pytest.fixture(scope="module", autouse=True)
 def gpu():
     if not torch.cuda.is_available():
@@ -105,7 +121,7 @@ def run_rs(n, count, dtype, seed, mode="persistent", inplace=False, sample=None,
         recv = torch.empty((n, count), dtype=TORCH[dtype], device=dev)
         recv.view(torch.uint8).fill_(0x7F)
         recvs = list(recv)
-    pat.check(pat.pat_set_exec_mode(mode))
+    set_mode(mode)
     stream = torch.cuda.current_stream()
     pat.check(pat.pat_reducescatter(list(send), recvs, count, dtype, pat.PAT_SUM, n, stream), "rs")
     pat.check(pat.pat_check_device_status(stream), "status")
@@ -131,7 +147,7 @@ def run_ag(n, count, dtype, seed, mode="persistent", inplace=False, dist=None):
         send = torch.empty((n, count), dtype=TORCH[dtype], device=dev)
         fill_ranks(send, dist, seed)
         sends = list(send)
-    pat.check(pat.pat_set_exec_mode(mode))
+    set_mode(mode)
     stream = torch.cuda.current_stream()
     pat.check(pat.pat_allgather(sends, list(recv), count, dtype, n, stream), "ag")
     pat.check(pat.pat_check_device_status(stream), "status")
@@ -154,7 +170,7 @@ def run_rs_modes(n, count, dtype, seed, modes, dist=None):
     for mode in modes:
         log(f"[gpu] reduce-scatter n={n} count={count} dtype={dtype} seed={seed:#x} mode={mode} (full output)")
         recv.view(torch.uint8).fill_(0x7F)
-        pat.check(pat.pat_set_exec_mode(mode))
+        set_mode(mode)
         pat.check(pat.pat_reducescatter(list(send), list(recv), count, dtype, pat.PAT_SUM, n, stream), "rs")
         pat.check(pat.pat_check_device_status(stream), "status")
         outs[mode] = as_bits(recv)
@@ -226,23 +242,28 @@ def test_workload2_ag_bf16_n24(mode):
 
 def test_workload3_rs_f32_n64_every_element():
     """Workload 3 at its full size (N = 64, 1 MiB output chunks): every output
-    element of every destination, in all four execution modes."""
+    element of every destination, in all four execution modes, stream mode as
+    a walk and as steps."""
     n, count, seed = 64, 262144, 0x5041543
-    outs = run_rs_modes(n, count, "float32", seed, ["stream", "graph", "persistent", "dataflow"])
+    outs = run_rs_modes(n, count, "float32", seed, ["stream", "steps", "graph", "persistent", "dataflow"])
     compare_rs_full(outs, n, count, "float32", "f32_normal", seed)
 
 
-@pytest.mark.parametrize("mode", ["stream", "graph", "persistent", "dataflow"])
+@pytest.mark.parametrize("mode", ["stream", "steps", "graph", "persistent", "dataflow"])
 def test_workload4_small_chunks_n1000(mode):
     """The small-size regime (N = 1000, 64 fp32 per chunk) as the benchmark
-    runs it (AUTO fusion: 10 steps in 3 launches in stream and graph modes):
-    the all-gather's whole output against the definition, and every one of the
+    runs it (AUTO fusion: one walk in stream mode, which graph mode and the
+    step schedule take in 3 launches for 10 steps): the all-gather's whole output against the definition, and every one of the
     reduce-scatter's 1000 x 64 outputs bit-exact against the PAT order and
     within 1e-5 of the fp64 sum."""
     n, count, seed = 1000, 64, 0x5041544
     assert pat.pat_get_top_fusion() == pat.PAT_FUSION_AUTO
     st, info = pat.pat_plan_info(pat.PAT_ALLGATHER, n, count, "float32")
     assert info["steps"] == 10 and info["launches_per_op"] == 3
+    set_mode(mode)
+    st, launched = pat.pat_launch_info(pat.PAT_ALLGATHER, n, count, "float32")
+    assert (launched["walk"], launched["launches"]) == {"stream": (1, 1), "steps": (0, 3), "graph": (0, 3)}.get(
+        mode, (0, 1))
     got, host_in = run_ag(n, count, "float32", seed, mode=mode, dist="f32_pm1")
     assert (got == host_in[None, :, :]).all()
     outs = run_rs_modes(n, count, "float32", seed + 100, [mode], dist="f32_pm1")
@@ -252,16 +273,16 @@ def test_workload4_small_chunks_n1000(mode):
 def test_workload5_rs_bf16_n128_every_element():
     """Workload 5 at its full size (N = 128, bf16 inputs, 4 MiB output chunks,
     64 GiB of send buffers): every one of the 128 x 2,097,152 outputs, in
-    stream, graph and dataflow modes, bit-exact against the PAT order and
-    within 1e-2 of the fp64 sum."""
+    stream (a walk, and as steps), graph and dataflow modes, bit-exact against
+    the PAT order and within 1e-2 of the fp64 sum."""
     n, count, seed = 128, 2 * MIB, 0x5041545
-    outs = run_rs_modes(n, count, "bfloat16", seed, ["stream", "graph", "dataflow"])
+    outs = run_rs_modes(n, count, "bfloat16", seed, ["stream", "steps", "graph", "dataflow"])
     pat.check(pat.pat_finalize())
     torch.cuda.empty_cache()
     compare_rs_full(outs, n, count, "bfloat16", "bf16_normal", seed)
 
 
-@pytest.mark.parametrize("mode", ["stream", "graph"])
+@pytest.mark.parametrize("mode", ["stream", "steps", "graph"])
 def test_workload7_ag_f32_n128_every_element(mode):
     """The bandwidth-regime all-gather at its benchmarked size (N = 128, 1 MiB
     chunks, 16 GiB of receive buffers): every element of every receive buffer
@@ -274,7 +295,7 @@ def test_workload7_ag_f32_n128_every_element(mode):
     fill_ranks(send, "f32_normal", seed)
     recv = torch.empty((n, n * count), dtype=torch.float32, device=dev)
     recv.view(torch.uint8).fill_(0xA5)
-    pat.check(pat.pat_set_exec_mode(mode))
+    set_mode(mode)
     stream = torch.cuda.current_stream()
     pat.check(pat.pat_allgather(list(send), list(recv), count, "float32", n, stream), "ag")
     pat.check(pat.pat_check_device_status(stream), "status")
@@ -291,7 +312,7 @@ def test_workload7_ag_f32_n128_every_element(mode):
 def test_maximum_rank_count():
     """N = 65536, the largest rank count the library accepts, with one-element
     chunks (16 GiB of rank buffers per collective, 128 KiB of slots per rank,
-    16 steps).  The oracle's executors are quadratic in N, so outputs are
+    16 steps; the all-gather also as one walk).  The oracle's executors are quadratic in N, so outputs are
     sampled: the all-gather at 200 000 (receiver, chunk) pairs against the
     definition; the reduce-scatter at 48 destination ranks, int32 against the
     wrapped plain sum and float32 bit-exact against the closed form of the
@@ -307,15 +328,17 @@ def test_maximum_rank_count():
     send = torch.empty((n, 1), dtype=torch.int32, device=dev)
     fill_ranks(send, "int32_pm2p20", seed)
     recv = torch.empty((n, n), dtype=torch.int32, device=dev)
-    recv.view(torch.uint8).fill_(0xA5)
-    pat.check(pat.pat_allgather(list(send), list(recv), 1, "int32", n, stream), "ag")
-    pat.check(pat.pat_check_device_status(stream), "status")
     xs = np.unique(np.concatenate([[0, 1, n - 1], rng.integers(0, n, 2000)]))
     want = {int(x): synth.host_values("int32_pm2p20", seed, int(x), np.zeros(1, dtype=np.uint64))[0] for x in xs}
     xx = rng.choice(xs, 200000)
     rr = rng.integers(0, n, 200000)
-    got = recv.view(-1)[torch.as_tensor(rr * n + xx, device=dev)].cpu().numpy()
-    np.testing.assert_array_equal(got, np.array([want[int(x)] for x in xx], dtype=np.int32))
+    for mode in ("steps", "stream"):
+        recv.view(torch.uint8).fill_(0xA5)
+        set_mode(mode)
+        pat.check(pat.pat_allgather(list(send), list(recv), 1, "int32", n, stream), "ag")
+        pat.check(pat.pat_check_device_status(stream), "status")
+        got = recv.view(-1)[torch.as_tensor(rr * n + xx, device=dev)].cpu().numpy()
+        np.testing.assert_array_equal(got, np.array([want[int(x)] for x in xx], dtype=np.int32))
     del send, recv
     pat.check(pat.pat_finalize())
     torch.cuda.empty_cache()
@@ -370,9 +393,11 @@ def test_sweep_default_budget(n, dtype, count, mode):
 
 @pytest.mark.parametrize("n", [5, 8, 13, 33])
 @pytest.mark.parametrize("budget", [4096, 16384, 65536])
-@pytest.mark.parametrize("mode", ["persistent", "graph", "stream", "dataflow"])
+@pytest.mark.parametrize("mode", ["persistent", "graph", "stream", "steps", "dataflow"])
 def test_sweep_budgets_and_modes(n, budget, mode):
-    count = 4104  # float32: 16416-byte chunks, so 4096 B forces pieces and a ragged last piece
+    # float32: 16416-byte chunks, so 4096 B forces pieces and a ragged last piece
+    # (which a walk, in stream mode, has none of: "steps" runs them there)
+    count = 4104
     pat.check(pat.pat_set_buffer_bytes(budget))
     try:
         for dtype in ("float32", "bfloat16"):
@@ -387,7 +412,7 @@ def test_sweep_budgets_and_modes(n, budget, mode):
 
 
 @pytest.mark.parametrize("count", [1000, 1001, 1004])  # aligned; partial last vectors; bf16 RS 4-element vectors
-@pytest.mark.parametrize("mode", ["stream", "graph", "persistent", "dataflow"])
+@pytest.mark.parametrize("mode", ["stream", "steps", "graph", "persistent", "dataflow"])
 @pytest.mark.parametrize("dtype", ["int32", "float32", "bfloat16"])
 @pytest.mark.parametrize("n", [1, 6, 9])
 def test_in_place(n, dtype, mode, count):
@@ -413,7 +438,7 @@ def test_repeated_calls_reuse_plan_and_tables():
                  oracle_t(pat.PAT_REDUCESCATTER, 12, 256, "float32"))
 
 
-@pytest.mark.parametrize("mode", ["stream", "graph"])
+@pytest.mark.parametrize("mode", ["stream", "steps", "graph"])
 @pytest.mark.parametrize("n", [6, 13, 33])
 @pytest.mark.parametrize("budget", [4096, 65536])
 def test_close_first_linear_order(n, budget, mode):
@@ -465,13 +490,13 @@ def test_persistent_barrier_timeout_is_reported_and_recovers():
              oracle_t(pat.PAT_REDUCESCATTER, n, count, "float32"))
 
 
-@pytest.mark.parametrize("mode", ["stream", "graph", "persistent", "dataflow"])
+@pytest.mark.parametrize("mode", ["stream", "steps", "graph", "persistent", "dataflow"])
 @pytest.mark.parametrize("n,K", [(12, 2), (24, 5), (64, 3), (100, 6), (128, 7)])
 @pytest.mark.parametrize("dtype", ["int32", "float32", "bfloat16"])
 def test_list_schedule_of_budget_aggregation(n, K, dtype, mode):
     """PAT_AGGREGATION_BUDGET with a budget of K chunks per step: the list
-    schedule (fewer steps than the power-of-two one here) against the oracle,
-    all-gather bit-exact, reduce-scatter bit-exact against the PAT order."""
+    schedule (fewer steps than the power-of-two one here; in stream mode a walk,
+    whatever the rule) against the oracle, all-gather bit-exact, reduce-scatter bit-exact against the PAT order."""
     count, seed = 1000, 0x1157 + n * 7 + K
     pat.check(pat.pat_set_aggregation("budget"))
     try:
@@ -640,18 +665,20 @@ def test_top_fusion_on_and_off(n, count, fusion, mode):
                                            (37, 1001, "bfloat16")])
 def test_top_fusion_is_bit_identical_to_step_kernels(n, count, dtype):
     """Same edges, same order of additions per element: fused and per-step
-    execution give the same bits, for both collectives."""
+    execution and a walk (AUTO in stream mode) give the same bits, for both
+    collectives."""
     seed = 0x70F + n
     outs = {}
-    for fusion in ("on", "off", "auto"):
+    for name, fusion, mode in (("on", "on", "stream"), ("off", "off", "stream"), ("auto", "auto", "steps"),
+                               ("walk", "auto", "stream")):
         pat.check(pat.pat_set_top_fusion(fusion))
         try:
-            ag, _ = run_ag(n, count, dtype, seed, mode="stream")
-            rs = run_rs(n, count, dtype, seed + 1, mode="stream")
+            ag, _ = run_ag(n, count, dtype, seed, mode=mode)
+            rs = run_rs(n, count, dtype, seed + 1, mode=mode)
         finally:
             pat.check(pat.pat_set_top_fusion("auto"))
-        outs[fusion] = (ag, rs)
-    for fusion in ("on", "auto"):
+        outs[name] = (ag, rs)
+    for fusion in ("on", "auto", "walk"):
         np.testing.assert_array_equal(outs[fusion][0], outs["off"][0])
         np.testing.assert_array_equal(outs[fusion][1], outs["off"][1])
     # and all of them against the oracle
@@ -1027,7 +1054,8 @@ def test_two_host_threads_on_their_own_streams():
 def test_large_rank_count_n2049():
     """N = 2049 (L = 12, not a power of two), full aggregation, tiny chunks:
     int32 and float32 reduce-scatter and all-gather on the 128-bit path
-    (4 elements) and the element path (3 elements), every output checked."""
+    (4 elements) and the element path (3 elements), every output checked; the
+    all-gathers as steps and as walks."""
     n = 2049
     got = run_rs(n, 4, "int32", 0x801, mode="stream")
     np.testing.assert_array_equal(got, D.reducescatter_sum(host_rs_inputs(n, 4, "int32_pm2p20", 0x801), "int32"))
@@ -1037,8 +1065,9 @@ def test_large_rank_count_n2049():
     scale = D.reducescatter_abs_sum(host_in, "float32")
     assert (np.abs(got.astype(np.float64) - exact) <= 1e-5 * scale).all()
     for count, dtype in ((3, "float32"), (8, "bfloat16")):
-        got, host_in = run_ag(n, count, dtype, 0x803 + count, mode="stream")
-        np.testing.assert_array_equal(got, D.allgather(host_in))
+        for mode in ("steps", "stream"):
+            got, host_in = run_ag(n, count, dtype, 0x803 + count, mode=mode)
+            np.testing.assert_array_equal(got, D.allgather(host_in))
     torch.cuda.empty_cache()
 
 
@@ -1093,19 +1122,19 @@ def _rows(flat, n, length, skew):
     return [flat[skew + r * length: skew + (r + 1) * length] for r in range(n)]
 
 
-@pytest.mark.parametrize("mode", ["stream", "graph", "persistent", "dataflow"])
+@pytest.mark.parametrize("mode", ["stream", "steps", "graph", "persistent", "dataflow"])
 @pytest.mark.parametrize("dtype", ["int32", "float32", "bfloat16"])
 def test_relaxed_vectors_at_element_offsets(dtype, mode):
     """Buffers one element past a 16-byte boundary, and counts just under,
     at and over one vector and one tile (a partial last vector that is the
     only vector, that closes a tile, that opens one), through the relaxed
-    128-bit kernels, against the oracle; plan_info reports the path
+    128-bit step kernels and the walks, against the oracle; plan_info reports the path
     16-byte-aligned buffers take."""
     es = {"int32": 4, "float32": 4, "bfloat16": 2}[dtype]
     per = 16 // es  # elements per all-gather vector
     counts = [per - 1, per, per + 1, 2 * per + 3, 2047, 2049, 4100, 4096 * 2 // es - 1]
     dev = torch.device("cuda:0")
-    pat.check(pat.pat_set_exec_mode(mode))
+    set_mode(mode)
     stream = torch.cuda.current_stream()
     dist = DIST[dtype]
     for n in (5, 16):
@@ -1218,15 +1247,19 @@ def test_random_skewed_buffers(case):
     ("ag", 128, 524288 - 3, "bfloat16", "stream"),
 ], ids=lambda c: "-".join(str(x) for x in c))
 def test_streaming_relaxed_kernels_full_size(case):
-    """Odd counts at the benchmarked sizes: the relaxed kernels in their
+    """Odd counts at the benchmarked sizes: the relaxed step kernels in their
     streaming (nontemporal) form, which only operations of 1e9 or more
-    algorithmic bytes use, against the oracle at every output element (every
-    chunk's partial last vector and the elements it overlaps included)."""
+    algorithmic bytes use, and the walks of the same operations, against the
+    oracle at every output element (every chunk's partial last vector and the
+    elements it overlaps included)."""
     coll, n, count, dtype, mode = case
+    modes = ["steps", "stream"] if mode == "stream" else [mode]
+    st, info = pat.pat_plan_info(pat.PAT_REDUCESCATTER if coll == "rs" else pat.PAT_ALLGATHER, n, count, dtype)
+    assert info["streaming"] == 1 and info["vector_path"] == 2
     seed = 0x0DD0 + count
     dist = DIST[dtype]
     if coll == "rs":
-        outs = run_rs_modes(n, count, dtype, seed, [mode])
+        outs = run_rs_modes(n, count, dtype, seed, modes)
         pat.check(pat.pat_finalize())
         torch.cuda.empty_cache()
         compare_rs_full(outs, n, count, dtype, dist, seed)
@@ -1236,17 +1269,18 @@ def test_streaming_relaxed_kernels_full_size(case):
         send = torch.empty((n, count), dtype=TORCH[dtype], device=dev)
         fill_ranks(send, dist, seed)
         recv = torch.empty((n, n * count), dtype=TORCH[dtype], device=dev)
-        recv.view(torch.uint8).fill_(0xA5)
-        pat.check(pat.pat_set_exec_mode(mode))
         stream = torch.cuda.current_stream()
-        pat.check(pat.pat_allgather(list(send), list(recv), count, dtype, n, stream), "ag")
-        pat.check(pat.pat_check_device_status(stream), "status")
         host_in = np.stack([synth.host_buffer(dist, seed, x, count) for x in range(n)])
         iview = torch.int16 if dtype == "bfloat16" else torch.int32
         want = torch.from_numpy(host_in.view(np.int16 if dtype == "bfloat16" else np.int32).reshape(-1)).to(dev)
         got = recv.view(iview)
-        bad = [r for r in range(n) if not torch.equal(got[r], want)]
-        assert not bad, f"receive buffers {bad[:8]} differ from the concatenation"
+        for m in modes:
+            recv.view(torch.uint8).fill_(0xA5)
+            set_mode(m)
+            pat.check(pat.pat_allgather(list(send), list(recv), count, dtype, n, stream), "ag")
+            pat.check(pat.pat_check_device_status(stream), "status")
+            bad = [r for r in range(n) if not torch.equal(got[r], want)]
+            assert not bad, f"{m}: receive buffers {bad[:8]} differ from the concatenation"
         del send, recv, want, got
     pat.check(pat.pat_finalize())
     torch.cuda.empty_cache()

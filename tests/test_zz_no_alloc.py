@@ -56,20 +56,25 @@ def oracle_check(got, n, count, dtype, dist, seed):
         assert (np.abs(val - exp["sum"]) <= tol * exp["abs"]).all()
 
 
-def test_noalloc_matches_the_allocating_entry_point():
+def test_noalloc_matches_the_allocating_entry_point(monkeypatch):
     dev = torch.device("cuda:0")
     stream = torch.cuda.current_stream()
     # (N, count, dtype, distribution, seed): the small-size regime (N = 1000,
     # 256 B chunks, about 122 MiB of slots), then a smaller bf16 operation with
     # an odd count (relaxed vectors, float32 root accumulators), then the first
     # shape again on new buffers and another mode setting (which the entry
-    # point ignores: it always launches per-step kernels).
+    # point ignores: it runs as stream mode does).  Each case runs its steps,
+    # then the default path: a walk but for the last, under 16 elements.  The
+    # reference is always the steps'.
     cases = [(1000, 64, "float32", "f32_pm1", 0x5041544, "stream"),
              (24, 1001, "bfloat16", "bf16_normal", 0x2401, "stream"),
              (1000, 64, "float32", "f32_pm1", 0x5041599, "graph"),
-             (7, 4096, "int32", "int32_pm2p20", 0x77, "persistent")]
-    for k, (n, count, dtype, dist, seed, mode) in enumerate(cases):
-        log(f"[gpu] noalloc call {k}: reduce-scatter n={n} count={count} {dtype} seed={seed:#x} mode={mode}")
+             (7, 4096, "int32", "int32_pm2p20", 0x77, "persistent"),
+             (33, 15, "bfloat16", "bf16_normal", 0x78, "stream")]
+    calls = [(path, c) for c in cases for path in ("steps", "default")]
+    for k, (path, (n, count, dtype, dist, seed, mode)) in enumerate(calls):
+        log(f"[gpu] noalloc call {k}: reduce-scatter n={n} count={count} {dtype} seed={seed:#x} mode={mode} {path}")
+        monkeypatch.setenv("PAT_WALK", "0")
         send = torch.empty((n, n * count), dtype=TORCH[dtype], device=dev)
         for x in range(n):
             synth.fill(send[x], dist, seed, x)
@@ -82,6 +87,12 @@ def test_noalloc_matches_the_allocating_entry_point():
         torch.cuda.synchronize()
         st, plans0, bytes0 = pat.pat_cache_stats()
         free0, _ = torch.cuda.mem_get_info()
+        if path == "default":
+            monkeypatch.delenv("PAT_WALK")
+            pat.check(pat.pat_set_exec_mode("stream"))
+            walk = pat.pat_launch_info(pat.PAT_REDUCESCATTER, n, count, dtype)[1]["walk"]
+            assert walk == (count >= 16)
+            pat.check(pat.pat_set_exec_mode(mode))
         pat.check(pat.pat_reducescatter_noalloc(S, O, count, dtype, pat.PAT_SUM, n, stream), "noalloc")
         torch.cuda.synchronize()
         free1, _ = torch.cuda.mem_get_info()
