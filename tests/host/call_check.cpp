@@ -159,11 +159,47 @@ static void check_routes() {
   EXPECT(pat_launch_info(PAT_ALLGATHER, 2, 1, PAT_FLOAT32, nullptr) == PAT_ERR_INVALID_ARGUMENT);
 }
 
+// Calls with buffers of their own, none waited for: every launch must find its
+// own call's addresses when it runs, also where the staging sets have come
+// round several times, and where calls that upload nothing come in between.
+static void check_staging() {
+  const int n = 70;  // more than a launch carries
+  const size_t count = 200;
+  for (int coll = 0; coll < 2; ++coll)
+    for (int mode : {PAT_EXEC_STREAM, PAT_EXEC_PERSISTENT, PAT_EXEC_DATAFLOW})
+      for (int fusion : {PAT_FUSION_AUTO, PAT_FUSION_OFF}) {
+        EXPECT(pat_set_exec_mode(mode) == PAT_OK && pat_set_top_fusion(fusion) == PAT_OK);
+        fake::forget();
+        std::vector<Buffers> made;
+        std::vector<size_t> first;
+        for (int k = 0; k < 23; ++k) {
+          made.push_back(buffers(coll, n, count * 4, (uintptr_t(1) << 40) + (uintptr_t(k) << 32)));
+          Buffers& b = made.back();
+          if (k % 5 != 3) {  // no spacing: the table has to be uploaded
+            std::swap(b.send[k + 1], b.send[k + 2]);
+            std::swap(b.recv[k + 3], b.recv[k + 40]);
+          }
+          if (k % 7 == 6) b = made[k - 1];  // the set of the call before
+          first.push_back(fake::launches.size());
+          EXPECT(call(coll, b, count, PAT_FLOAT32) == PAT_OK);
+        }
+        first.push_back(fake::launches.size());
+        fake::drain();
+        for (size_t k = 0; k < made.size(); ++k) {
+          EXPECT(first[k + 1] > first[k]);
+          for (size_t j = first[k]; j < first[k + 1]; ++j)
+            EXPECT(fake::launches[j].send == made[k].send && fake::launches[j].recv == made[k].recv);
+        }
+      }
+  EXPECT(pat_set_exec_mode(PAT_EXEC_STREAM) == PAT_OK && pat_set_top_fusion(PAT_FUSION_AUTO) == PAT_OK);
+}
+
 int main(int argc, char** argv) {
   const std::string which = argc > 1 ? argv[1] : "";
   if (which == "no_environment") check_no_environment();
   else if (which == "trace") check_trace();
   else if (which == "routes") check_routes();
+  else if (which == "staging") check_staging();
   else return std::fprintf(stderr, "no check named '%s'\n", which.c_str()), 2;
   EXPECT(pat_finalize() == PAT_OK);
   std::printf("%s: %d failures\n", which.c_str(), failures);

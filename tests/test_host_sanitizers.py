@@ -65,12 +65,13 @@ def call_check(tmp_path_factory):
     return str(exe)
 
 
-@pytest.mark.parametrize("check", ["no_environment", "trace", "routes"])
+@pytest.mark.parametrize("check", ["no_environment", "trace", "routes", "staging"])
 def test_whole_calls_over_a_fake_runtime(call_check, check):
     """Whole calls on the CPU, with the launches they make and the addresses
     those find.  no_environment: a process without any environment.  trace:
     which launches the two trace starts record.  routes: pat_launch_info says
-    what calls launch, on both sides of every limit and at every setting."""
+    what calls launch, on both sides of every limit and at every setting.
+    staging: queued calls find their own buffers' addresses."""
     env = {k: v for k, v in os.environ.items() if not k.startswith("PAT_")}
     res = subprocess.run([call_check, check], capture_output=True, text=True, timeout=600, env=env)
     assert res.returncode == 0, (res.stdout[-1000:], res.stderr[-3000:])

@@ -144,6 +144,12 @@ def test_overlap_checks_agree_with_the_definition():
     (1033, 20, "float32", "shuffled"), (1030, 17, "bfloat16", "shuffled"), (1034, 18, "bfloat16", "separate"),
     (200, 1320, "int32", "shuffled"), (300, 519, "bfloat16", "shuffled"), (250, 1058, "bfloat16", "shuffled"),
     (128, 4118, "bfloat16", "shuffled"), (7, 30, "float32", "shuffled"),
+    # keyed read orders in workgroups of 256 lanes: 2 lane groups and nontemporal
+    # accesses, 4 and cached ones
+    (128, 4096, "float32", "rows"), (32, 2048, "float32", "rows"), (64, 4096, "int32", "rows"),
+    # a chunk's own workgroups: many lane groups, pointer tables
+    (300, 1024, "float32", "rows"), (300, 1000, "float32", "shuffled"), (100, 4096, "int32", "shuffled"),
+    (257, 1000, "bfloat16", "shuffled"), (600, 260, "bfloat16", "reversed"),
 ])
 @pytest.mark.parametrize("entry", ["reducescatter", "reducescatter_noalloc"])
 def test_walked_reducescatter(n, count, dtype, layout, entry):
@@ -234,12 +240,21 @@ def test_walk_over_a_pointer_table_is_not_the_slower_path(monkeypatch):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n,count,dtype", [(7, 1001, "float32"), (40, 203, "bfloat16"), (12, 64, "int32")])
-def test_walked_reducescatter_in_place_and_special_values(n, count, dtype):
+@pytest.mark.parametrize("n,count,dtype,order", [
+    (7, 1001, "float32", "rows"), (40, 203, "bfloat16", "rows"), (12, 64, "int32", "rows"),
+    # keyed orders, 2 and 8 lane groups; pointer tables, chunks that share a
+    # workgroup or fill their own; a whole tree in many workgroups
+    (128, 4096, "float32", "rows"), (128, 1024, "int32", "rows"), (66, 33, "float32", "shuffled"),
+    (100, 4099, "bfloat16", "shuffled"), (9, 500003, "float32", "rows"), (40, 77, "int32", "shuffled"),
+])
+def test_walked_reducescatter_in_place_and_special_values(n, count, dtype, order):
     """In place (rank r receives into its own chunk r), with infinities, NaN,
     negative zeros and subnormals among the inputs: the step kernels' bits
     (any NaN for a NaN), and send buffers otherwise untouched."""
-    print(f"[gpu] walk in place n={n} count={count} {dtype}", file=sys.stderr, flush=True)
+    print(f"[gpu] walk in place n={n} count={count} {dtype} {order}", file=sys.stderr, flush=True)
+    row = list(range(n))  # rank r's buffer is row row[r]
+    if order == "shuffled":
+        row = [int(x) for x in np.random.default_rng(n).permutation(n)]
     pat.check(pat.pat_set_exec_mode("stream"))
     stream = torch.cuda.current_stream()
     gen = torch.Generator(device="cuda:0").manual_seed(5)
@@ -256,23 +271,95 @@ def test_walked_reducescatter_in_place_and_special_values(n, count, dtype):
         send = src.clone()
         pat.check(pat.pat_set_top_fusion(fusion))
         try:
-            pat.check(pat.pat_reducescatter(list(send), [send[r, r * count:] for r in range(n)], count, dtype,
-                                            pat.PAT_SUM, n, stream))
+            pat.check(pat.pat_reducescatter([send[x] for x in row], [send[x, r * count:] for r, x in enumerate(row)],
+                                            count, dtype, pat.PAT_SUM, n, stream))
             torch.cuda.synchronize()
         finally:
             pat.check(pat.pat_set_top_fusion("auto"))
         got.append(send)
-    for r in range(n):  # only chunk r of row r may change
+    for r, x in enumerate(row):  # only chunk r of rank r's row may change
         for t in got:
-            same = torch.ones(n * count, dtype=torch.bool, device="cuda:0")
-            same[r * count:(r + 1) * count] = False
-            assert torch.equal(t[r][same].view(torch.uint8), src[r][same].view(torch.uint8))
+            for part in (slice(0, r * count), slice((r + 1) * count, None)):
+                assert torch.equal(t[x, part].view(torch.uint8), src[x, part].view(torch.uint8))
     a, b = (t.clone() for t in got)
     if dtype != "int32":
         assert torch.equal(a.isnan(), b.isnan())
         a[a.isnan()] = 0
         b[b.isnan()] = 0
     assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("path", ["steps", "walk over a table"])
+def test_pointer_tables_of_queued_calls(path, monkeypatch):
+    """Eleven calls on one plan, each with buffers of its own, queued behind
+    work that takes longer than queueing them: the library's four staging sets
+    come round again while earlier uploads are still pending, and every call
+    must still find its own addresses."""
+    n, count, calls = 70, 200, 11
+    print(f"[gpu] queued calls n={n} count={count} {path}", file=sys.stderr, flush=True)
+    if path == "steps":
+        monkeypatch.setenv("PAT_WALK", "0")
+    pat.check(pat.pat_set_exec_mode("stream"))
+    stream = torch.cuda.current_stream()
+    bufs = [(rows(n, n * count, "float32", "shuffled"), rows(n, count, "float32", "shuffled")) for _ in range(calls)]
+    for k, (send, recv) in enumerate(bufs):
+        for x in range(n):
+            synth.fill(send[x], "f32_normal", 40 + k, x)
+            recv[x].fill_(float("nan"))
+    args = [(pat.pointer_array(send), pat.pointer_array(recv)) for send, recv in bufs]
+    pat.check(pat.pat_reducescatter(*args[0], count, "float32", pat.PAT_SUM, n, stream))  # the plan is made
+    bufs[0][1][0].fill_(float("nan"))
+    busy = torch.zeros(1 << 28, device="cuda:0")
+    torch.cuda.synchronize()
+    for _ in range(50):  # about 20 ms
+        busy.add_(1)
+    for S, R in args:
+        pat.check(pat.pat_reducescatter(S, R, count, "float32", pat.PAT_SUM, n, stream))
+    torch.cuda.synchronize()
+    for k, (_, recv) in enumerate(bufs):
+        want = native.reducescatter("float32", n, count, dist="f32_normal", seed=40 + k)["pat"]
+        np.testing.assert_array_equal(np.stack([bits(r) for r in recv]), want.view(np.uint32).reshape(n, count))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,count,dtype,layout", [
+    (6, 1024, "int32", "rows"), (24, 1001, "bfloat16", "separate"), (128, 4096, "float32", "rows"),
+    (70, 100, "float32", "shuffled"),
+])
+def test_captured_walks(n, count, dtype, layout):
+    """The no-allocation entry point under graph capture, as a walk: addresses
+    at a stride, in the launch, and in the library's table (after a call that
+    put them there).  Replays between eager work and synchronizations, each on
+    new inputs, give the eager call's bits."""
+    print(f"[gpu] captured walk n={n} count={count} {dtype} {layout}", file=sys.stderr, flush=True)
+    pat.check(pat.pat_set_exec_mode("stream"))
+    assert pat.pat_launch_info(pat.PAT_REDUCESCATTER, n, count, dtype)[1]["walk"] == 1
+    send, recv = rows(n, n * count, dtype, layout), rows(n, count, dtype, layout)
+    eager = rows(n, count, dtype, "rows")
+    S, R, E = (pat.pointer_array(b) for b in (send, recv, eager))
+    for x in range(n):
+        synth.fill(send[x], DIST[dtype], 1, x)
+    stream = torch.cuda.current_stream()
+    pat.check(pat.pat_reducescatter_noalloc(S, R, count, dtype, pat.PAT_SUM, n, stream))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        st = pat.pat_reducescatter_noalloc(S, R, count, dtype, pat.PAT_SUM, n, torch.cuda.current_stream())
+    pat.check(st)
+    for rep in range(4):
+        for x in range(n):
+            synth.fill(send[x], DIST[dtype], 100 + rep, x)
+            recv[x].view(torch.uint8).fill_(0xA5)
+        graph.replay()
+        if rep % 2:
+            torch.cuda.synchronize()
+        pat.check(pat.pat_reducescatter(S, E, count, dtype, pat.PAT_SUM, n, stream))
+        torch.cuda.synchronize()
+        for x in range(n):
+            np.testing.assert_array_equal(bits(recv[x]), bits(eager[x]))
+        want = native.reducescatter(dtype, n, count, dist=DIST[dtype], seed=100 + rep)["pat"]
+        np.testing.assert_array_equal(np.stack([bits(r) for r in recv]), want.view(WIDTH[dtype]).reshape(n, count))
 
 
 @pytest.mark.gpu
