@@ -70,7 +70,7 @@ WORKLOADS = {
 _CSRC = "paper_2506_20252_amd/csrc/"
 KERNEL_SOURCES = {
     "step": [_CSRC + f for f in ("kernels.hip", "device_access.hpp", "kernels.hpp", "device_types.hpp")],
-    "walk": [_CSRC + f for f in ("walk.hip", "walk.hpp", "device_access.hpp")],
+    "walk": [_CSRC + f for f in ("walk.hip", "walk_shape.hpp", "walk.hpp", "device_access.hpp")],
 }
 
 

@@ -19,13 +19,13 @@
 
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cstddef>
 #include <cstring>
 #include <type_traits>
 
 #include "device_access.hpp"
 #include "walk.hpp"
+#include "walk_shape.hpp"
 
 namespace pat {
 namespace {
@@ -46,20 +46,6 @@ struct RowPointers {
 // loads serve where the rank is uniform.
 #define PAT_CONSTANT __attribute__((address_space(4)))
 typedef const PAT_CONSTANT uint64_t* RowTable;
-
-// The workgroups of an operation.  They go to the 8 XCDs round-robin; each XCD
-// takes runs of `grain` consecutive blocks.
-struct Blocks {
-  uint32_t count;  // in all
-  uint32_t grain;
-  uint32_t first;  // of this launch: a multiple of 8 * grain
-};
-
-// This workgroup's block; past `count`: none.
-__device__ __forceinline__ uint32_t block_of(const Blocks& b) {
-  const uint32_t x = blockIdx.x % 8, j = blockIdx.x / 8;
-  return b.first + (j / b.grain) * 8 * b.grain + x * b.grain + j % b.grain;
-}
 
 // A kernel's one argument: the pointers' place in the argument segment is
 // then known.
@@ -91,16 +77,13 @@ __device__ __forceinline__ char* recv_row(const Ctx& cx, int r) {
   return (char*)row_table<Ctx>(cx.rows.recv_table, offsetof(RowPointers, recv))[r];
 }
 
-// Launches the blocks of cx: in one launch up to 2^31 lanes (a grid's limit is
-// 2^32 in each dimension), else in several.
+// Launches the blocks of cx, in as many launches as it takes.
 template <class Arg, class Ctx>
 void launch_blocks(void (*kernel)(Arg), int threads, Arg& arg, Ctx& cx, hipStream_t stream) {
-  const uint64_t run = 8ull * cx.blocks.grain, most = (uint64_t(1) << 31) / threads / run * run;
-  for (uint64_t first = 0; first < cx.blocks.count; first += most) {
-    const uint64_t n = std::min<uint64_t>(most, cx.blocks.count - first);
-    cx.blocks.first = (uint32_t)first;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + run - 1) / run * run)), dim3(threads), 0, stream, arg);
-  }
+  each_launch(cx.blocks, threads, [&](const Blocks& b, uint32_t grid) {
+    cx.blocks = b;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, arg);
+  });
 }
 
 template <class Ctx, bool SPACED>
@@ -268,23 +251,12 @@ __global__ __launch_bounds__(MAXT) void walk_rs_kernel(WalkArgs<WalkCtx, SPACED>
     s = __builtin_amdgcn_readfirstlane(threadIdx.x / lanes);
     lane = threadIdx.x - s * lanes;
   }
-  const uint32_t blk = block_of(cx.blocks);
+  const uint32_t blk = block_of(cx.blocks, blockIdx.x);
   if (blk >= cx.blocks.count) return;
   int R;
   int64_t v;
-  bool live;
-  if constexpr (UNI) {
-    R = (int)(blk / cx.tiles);
-    v = (int64_t)(blk - (uint32_t)R * cx.tiles) * lanes + lane;
-    live = v < cx.V;
-  } else {
-    // Chunks share workgroups only below 8 * lanes <= 2048 vectors, and there
-    // are at most kWalkMostRanks: 32 bits hold every index.
-    const uint32_t f = blk * (uint32_t)lanes + (uint32_t)lane;
-    live = f < (uint32_t)cx.N * (uint32_t)cx.V;
-    R = (int)(f / (uint32_t)cx.V);
-    v = f - (uint32_t)R * (uint32_t)cx.V;
-  }
+  const bool live = UNI ? own_vector(blk, lane, lanes, cx.tiles, cx.V, &R, &v)
+                        : shared_vector(blk, lane, lanes, cx.N, cx.V, &R, &v);
   const bool part = cx.back && v == cx.V - 1;
   const int64_t voff = v * (int64_t)sizeof(in_t) - (part ? cx.back * T::kElem : 0);
   const int64_t soff = (int64_t)R * cx.chunk_bytes + voff;
@@ -404,101 +376,22 @@ void launch_walk_rs_k(const WalkCtx& cx, const WalkRows& rows, bool uni, bool ke
     launch_kernel(walk_rs_kernel<T, G, MAXT, LV, SPLIT, false, false, false, NT>, threads, cx, rows, stream);
 }
 
-// Slots of a lane group: the sub-tree it walks spans at most 2^(slots - 1)
-// groups of positions.
-template <class T>
-constexpr int walk_slots(int S) {
-  return S <= 4 ? 6 : 8;
-}
-// Positions read at a time.  A whole tree: 4.  A part of one: float32 and
-// int32 2, bf16 4.  VGPRs of a part's kernels, with a chunk's own workgroups /
-// shared ones: float32 56 / 62-70 at 256 lanes, 64 / 70-78 at 1024; bf16 66 /
-// 74-82 and 74 / 79-90 (64 leave 8 waves per SIMD, 72 7, 80 6, 96 5).
-template <class T>
-constexpr int walk_group(int S) {
-  return S == 1 || T::kElem == 2 ? 4 : 2;
-}
-
-// S: lane groups per vector.  One reads a whole tree where that alone gives
-// enough waves: walk_waves, about what keeps HBM busy.  Fewer leave it waiting,
-// more cost an LDS exchange per vector and shorter walks.  A group keeps at
-// least kWalkSpan positions (two to four rounds of loads), and at most what its
-// slots hold.  Measured on MI355X, us at S = 1, 2, 4, 8, 16 (waves at S = 1):
-//   float32  N=50 20 KB (976) 17, 14, 10.5, 10.5, 12; N=500 1200 B (585) -, -,
-//            61, 56, 64; N=100 40 KB (3906) 68, 65, 64, 69, 75; N=10 1 MiB
-//            (10240) 21, 24, 26, 37, 60
-//   bf16     N=64 32 KiB (4096) 24, 25, 24, 27, 48; N=24 64 KiB (3072) 8.4, 9.3,
-//            9.6, 14, 28; N=200 666 B (262) 30, 21, 12, 9.4, 10.9
-// A bf16 walk over rows off an 8-byte boundary, whose accesses are split, is
-// faster in two parts when it is large: N=64 262143 elements 503, 432 us.
-//
-// Workgroups of 256 lanes.  For large whole-tree walks wider ones are slower and
-// narrower ones no different, us at 256 lanes / at another width, side by side:
-//   N=64 float32 1 MiB    64: 653, 648   128: 657, 634   512: 640, 705   1024: 657, 700
-//   N=128 bf16 4 MiB, ms  64: 10.7, 10.6 128: 10.3, 10.5 512: 10.6, 10.7 1024: 10.7, 11.0
-//   N=64 float32 262143   64: 692, 682   128: 675, 687   512: 682, 745   1024: 681, 739
-// (two runs of one width differ by up to 4%, once 6%).
-//
-// Order of the workgroups: each XCD takes runs of `grain` consecutive blocks,
-// whose rows then cover its L2's channels evenly; one by one, blocks of 1 KiB
-// per row keep an XCD on the same few channels (N=64 bf16 32 KiB at S = 4 35
-// against 23 us).  Long runs also keep an XCD on fewer pages: N=128 bf16 4 MiB
-// 13.0 ms one by one, 12.0, 11.9, 11.8 ms with runs of 16, 64, 256; short ones
-// leave a small grid balanced (N=300 float32 4 KiB, 1200 blocks: 75 us with
-// runs of 4, 126 with 64).
-template <class T>
-constexpr int64_t walk_waves() {
-  return T::kElem == 2 ? 2048 : 4096;
-}
-constexpr int kWalkSpan = 8;
-constexpr int kWalkMostGroups = 16;
-
-// Whether the parts of a tree are read in keyed orders.  Position q of chunk R
-// is at row (R + q) * spacing + R * chunk: with both sizes powers of two and
-// all workgroups at the same q, R and R + q fall on address bits that the
-// memory channels' hash combines, and the reads crowd on few channels; a key
-// per workgroup spreads q.  Measured on MI355X for float32, plain / keyed order
-// at the S in use: N=128, 16 KiB chunks (2 MiB rows) 58.6 / 44.6 us, 8 KiB 28.1
-// / 24.1, 4 KiB 15.2 / 12.3; N=1024 256 B 50.8 / 45.9; N=64 4 KiB 6.6 / 6.0;
-// N=32 16 KiB 6.1 / 6.0.  Beyond, where a workgroup's neighbours cover the
-// channels by themselves, plain order is faster: N=64 32 KiB 24.1 / 25.0, N=256
-// 16 KiB (4 MiB rows) 168 / 171, N=64 1 MiB 625 / 668, N=1024 64 B (64 KiB
-// rows) 23.6 / 27.3; so it is for rows of other spacings (N=128 16000 B 42.3 /
-// 44.0, N=100 16 KiB 27.3 / 28.2) and for bf16 (N=128 16 KiB 46.8 / 53.1).
-bool walk_keyed(const WalkCtx& cx, const WalkRows& rows) {
-  auto pow2 = [](int64_t v) { return v > 0 && (v & (v - 1)) == 0; };
-  return rows.spaced && pow2(cx.N) && pow2(rows.send_stride) && pow2(cx.chunk_bytes) && cx.chunk_bytes <= 16384 &&
-         rows.send_stride >= (256 << 10) && rows.send_stride <= (2 << 20);
-}
-
 template <class T, bool NT>
 hipError_t launch_walk_rs_t(WalkCtx cx, const WalkRows& rows, hipStream_t stream) {
-  int span = 1;
-  while (span < cx.N) span *= 2;
-  const int64_t waves = (cx.N * cx.V + 63) / 64;
-  auto holds = [&](int S) { return span / S <= walk_group<T>(S) << (walk_slots<T>(S) - 1); };
-  int S = 1;
-  while (S < kWalkMostGroups && ((waves * S < walk_waves<T>() && span / S > kWalkSpan) || !holds(S))) S *= 2;
-  const bool split_rows = T::kElem == 2 && (!rows.aligned8 || cx.chunk_bytes % 8);
-  if (split_rows && S == 1 && waves >= 16384 && span > kWalkSpan) S = 2;
-  if (!holds(S)) return hipErrorInvalidValue;
-  const int threads = S <= 4 ? 256 : 64 * S;
-  cx.lanes = threads / S;
-  cx.w = span / S;
-  const int64_t tiles = (cx.V + cx.lanes - 1) / cx.lanes;
-  // A chunk's vectors fill its own workgroups unless that leaves too many lanes idle.
-  const bool uni = tiles * cx.lanes <= cx.V + cx.V / 8;
-  const int64_t blocks = uni ? tiles * cx.N : (cx.N * cx.V + cx.lanes - 1) / cx.lanes;
-  if (blocks > (int64_t(1) << 31)) return hipErrorInvalidValue;
-  cx.tiles = (uint32_t)tiles;
-  cx.blocks = {(uint32_t)blocks, blocks >= 16384 ? 64u : 4u, 0};
-  const bool keyed = walk_keyed(cx, rows) && cx.w >= walk_group<T>(S);
+  ReduceShape sh;
+  if (!reduce_shape(cx.N, cx.V, cx.chunk_bytes, T::kElem, rows, &sh)) return hipErrorInvalidValue;
+  const int S = sh.S, threads = sh.threads;
+  const bool uni = sh.uni, keyed = sh.keyed;
+  cx.lanes = sh.lanes;
+  cx.w = sh.w;
+  cx.tiles = sh.tiles;
+  cx.blocks = sh.blocks;
   if (S == 1)
-    launch_walk_rs_k<T, walk_group<T>(1), 256, walk_slots<T>(1), false, NT>(cx, rows, uni, keyed, threads, stream);
+    launch_walk_rs_k<T, walk_group(T::kElem, 1), 256, walk_slots(1), false, NT>(cx, rows, uni, keyed, threads, stream);
   else if (S <= 4)
-    launch_walk_rs_k<T, walk_group<T>(4), 256, walk_slots<T>(4), true, NT>(cx, rows, uni, keyed, threads, stream);
+    launch_walk_rs_k<T, walk_group(T::kElem, 4), 256, walk_slots(4), true, NT>(cx, rows, uni, keyed, threads, stream);
   else
-    launch_walk_rs_k<T, walk_group<T>(16), 1024, walk_slots<T>(16), true, NT>(cx, rows, uni, keyed, threads, stream);
+    launch_walk_rs_k<T, walk_group(T::kElem, 16), 1024, walk_slots(16), true, NT>(cx, rows, uni, keyed, threads, stream);
   return hipGetLastError();
 }
 
@@ -521,9 +414,6 @@ struct GatherCtx {
   Blocks blocks;
 };
 
-constexpr int kGatherThreads = 256;
-constexpr int kGatherTile = kGatherThreads * 16;  // bytes
-
 // The bound is HBM's write rate.  A tile's vectors start where the
 // workgroup's first receiver has a 128-byte line, so that its stores write
 // whole lines also where rows start in the middle of one (then the first tile
@@ -542,11 +432,11 @@ __global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(WalkArgs<Gather
   const GatherCtx& cx = args.cx;
   constexpr int kElems = 16 / ES;
   using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
-  const uint32_t blk = block_of(cx.blocks);
+  const uint32_t blk = block_of(cx.blocks, blockIdx.x);
   if (blk >= cx.blocks.count) return;
-  const uint32_t g = blk / cx.tiles, tile = blk - g * cx.tiles;
-  // receivers r0, r0 + period, ...: `run` of them
-  const int turn = (int)g / cx.period, r0 = (int)g - turn * cx.period + turn * cx.run * cx.period;
+  uint32_t tile;
+  int r0;  // receivers r0, r0 + period, ...: `run` of them
+  gather_block(blk, cx.tiles, cx.period, cx.run, &tile, &r0);
   if (r0 >= cx.N) return;
   const int64_t C = cx.chunk_bytes;
   const int64_t tile0 = (int64_t)tile * kGatherTile - (int64_t)((uintptr_t)recv_row<SPACED>(cx, r0) & 127);  // may be negative
@@ -603,37 +493,13 @@ __global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(WalkArgs<Gather
   }
 }
 
-// Receivers per workgroup: as many as make one round of workgroups
-// (kGatherBlocks, what the chip holds) out of a small operation, at most 4.
-// One receiver each costs a chain of dependent loads per vector (N=24 bf16 64
-// KiB: 1, 2, 3, 4, 6 receivers 15.2, 8.0, 7.9, 7.8, 8.1 us); more than 4 only
-// write more rows at once (N=300 float32 4 KiB: 4, 6, 8 receivers 56, 60, 60
-// us; N=1000 252 B: 39, 42, 44 us).  A tiny operation is best spread (N=13 bf16
-// 2002 B: 3.8, 4.1, 4.8 us at 1, 2, 4).
-constexpr int kGatherRun = 4;
-constexpr int64_t kGatherBlocks = 2048;
-
 hipError_t launch_walk_ag(GatherCtx cx, const WalkRows& rows, int esize, hipStream_t stream) {
-  const int64_t recv_stride = rows.recv_stride;
-  // Rows a period apart start at the same offset from a line.  With too few
-  // rows for that to leave kGatherRun in a class, neighbours share a workgroup
-  // (N=37 float32 9999 elements, period 32: 13 us against 28 us apart).
-  cx.period = 1;
-  for (int64_t s = recv_stride % 128; s % 128; s += recv_stride % 128) ++cx.period;
-  if (cx.period * kGatherRun > cx.N) cx.period = 1;
-  // a tile more for rows that start up to 127 bytes past a line
-  const int64_t tiles = (cx.row_bytes + 127 + kGatherTile - 1) / kGatherTile;
-  cx.run = (int32_t)std::min<int64_t>(kGatherRun, (tiles * cx.N + kGatherBlocks - 1) / kGatherBlocks);
-  const int64_t turns = ((cx.N + cx.period - 1) / cx.period + cx.run - 1) / cx.run;
-  const int64_t blocks = tiles * turns * cx.period;
-  if (blocks > (int64_t(1) << 31)) return hipErrorInvalidValue;
-  cx.tiles = (uint32_t)tiles;
-  // Order: tiles of the same receivers follow each other.  Runs of them per
-  // XCD for large operations only (in place, one by one / runs of 256: N=128
-  // float32 1 MiB, 1.05 M blocks, 3080 / 2760 us; N=50 float32 400 KB 163 / 162
-  // us; N=300 float32 4 KiB, 22500 blocks, 51 / 65 us; but N=700 bf16 32 KiB
-  // 2530 / 2630 us).
-  cx.blocks = {(uint32_t)blocks, blocks >= (1 << 18) ? 256u : 1u, 0};
+  GatherShape sh;
+  if (!gather_shape(cx.N, cx.row_bytes, rows.recv_stride, &sh)) return hipErrorInvalidValue;
+  cx.period = sh.period;
+  cx.run = sh.run;
+  cx.tiles = sh.tiles;
+  cx.blocks = sh.blocks;
   if (rows.spaced)
     launch_kernel(esize == 2 ? walk_ag_kernel<2, true> : walk_ag_kernel<4, true>, kGatherThreads, cx, rows, stream);
   else
@@ -658,11 +524,11 @@ struct CopyCtx {
 template <int ES>
 __global__ __launch_bounds__(kGatherThreads) void walk_ag_rows_kernel(CopyCtx cx) {
   using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
-  const uint32_t blk = block_of(cx.blocks);
+  const uint32_t blk = block_of(cx.blocks, blockIdx.x);
   if (blk >= cx.blocks.count) return;
-  const uint32_t g = blk / cx.panel;  // (panel, receiver, tile of the panel)
-  const uint32_t p = g / cx.N, tile = p * cx.panel + (blk - g * cx.panel);
-  char* const row = (char*)(cx.recv0 + (uint64_t)((int64_t)(g - p * cx.N) * cx.recv_stride));
+  uint32_t tile, receiver;
+  copy_block(blk, cx.panel, cx.N, &tile, &receiver);
+  char* const row = (char*)(cx.recv0 + (uint64_t)((int64_t)receiver * cx.recv_stride));
   const char* const src = (const char*)cx.send0;
   const int64_t tile0 = (int64_t)tile * kGatherTile - (int64_t)((uintptr_t)row & 127);  // may be negative
   const int64_t o = tile0 + (int)threadIdx.x * 16;
@@ -674,36 +540,11 @@ __global__ __launch_bounds__(kGatherThreads) void walk_ag_rows_kernel(CopyCtx cx
   }
 }
 
-// Order of the workgroups.  A panel of the concatenation (at most kCopyPanel
-// tiles, 2 MiB) goes to every receiver before the next panel, and an XCD takes
-// the same eighth of it for each of them: its L2 then serves the panel's reads
-// but the first.  Measured on MI355X, us with the tiles of four receivers in a
-// loop (walk_ag_kernel) / in this order: N=128 float32 1 MiB 2937 / 2449 (7.0
-// TB/s written), N=700 bf16 32 KiB 2745 / 2239, N=128 bf16 262143 elements 1470 /
-// 1178, N=50 float32 400 KB 177 / 142, N=8 bf16 1000001 elements 29 / 20, N=24
-// bf16 64 KiB 8.5 / 7.6.  With XCD runs that do not repeat from one receiver to
-// the next: 2600, 2333, 1231, 157, 33, 8.2.  A concatenation under
-// kCopyLeastPanels tiles is in every L2 soon; there longer runs across the
-// receivers' rows are faster (N=5000 float32 64 B: 220 against 267 us, loop 265;
-// N=1024 bf16 38 B 7.9, 11.4, 10.6; N=100 bf16 6666 B 10.9, 12.0, 14.0; N=1000
-// float32 256 B 39, 37, 42).
-constexpr int64_t kCopyPanel = 512;
-constexpr int64_t kCopyLeastPanels = 256;
-
 hipError_t launch_walk_ag_rows(const GatherCtx& gx, const WalkRows& rows, int esize, hipStream_t stream) {
-  CopyCtx cx{(uint64_t)rows.send[0], (uint64_t)rows.recv[0], rows.recv_stride, gx.row_bytes, (uint32_t)gx.N, 0, {}};
-  // a tile more for rows that start up to 127 bytes past a line
-  const int64_t tiles = (gx.row_bytes + 127 + kGatherTile - 1) / kGatherTile;
-  const int64_t panels = (tiles + kCopyPanel - 1) / kCopyPanel;
-  int64_t grain = ((tiles + panels - 1) / panels + 7) / 8;
-  cx.panel = (uint32_t)(8 * grain);
-  if (tiles < kCopyLeastPanels) {
-    cx.panel = (uint32_t)tiles;
-    grain = tiles * gx.N >= 65536 ? 64 : 16;
-  }
-  const int64_t blocks = panels * cx.panel * gx.N;
-  if (blocks > (int64_t(1) << 31)) return hipErrorInvalidValue;
-  cx.blocks = {(uint32_t)blocks, (uint32_t)grain, 0};
+  CopyShape sh;
+  if (!copy_shape(gx.N, gx.row_bytes, &sh)) return hipErrorInvalidValue;
+  CopyCtx cx{(uint64_t)rows.send[0], (uint64_t)rows.recv[0], rows.recv_stride, gx.row_bytes, (uint32_t)gx.N, sh.panel,
+             sh.blocks};
   launch_blocks(esize == 2 ? walk_ag_rows_kernel<2> : walk_ag_rows_kernel<4>, kGatherThreads, cx, cx, stream);
   return hipGetLastError();
 }

@@ -1,0 +1,262 @@
+// The launches of the walk kernels: how an operation is cut into workgroups, and
+// which part of it a workgroup's index stands for.  Plain arithmetic, shared by
+// the kernels and the host.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+#include "walk.hpp"
+
+#ifdef __HIPCC__
+#define PAT_BOTH __host__ __device__ __forceinline__
+#else
+#define PAT_BOTH inline
+#endif
+
+namespace pat {
+
+// The workgroups of an operation.  They go to the 8 XCDs round-robin; each XCD
+// takes runs of `grain` consecutive blocks.
+struct Blocks {
+  uint32_t count;  // in all
+  uint32_t grain;
+  uint32_t first;  // of this launch: a multiple of 8 * grain
+};
+
+// The block of workgroup `index` of a launch; past `count`: none.
+PAT_BOTH uint32_t block_of(const Blocks& b, uint32_t index) {
+  const uint32_t x = index % 8, j = index / 8;
+  return b.first + (j / b.grain) * 8 * b.grain + x * b.grain + j % b.grain;
+}
+
+// Calls launch(blocks, grid) for the launches of an operation: one up to 2^31
+// lanes (a grid's limit is 2^32 in each dimension), else several.
+template <class F>
+void each_launch(Blocks b, int threads, F launch) {
+  const uint64_t run = 8ull * b.grain, most = (uint64_t(1) << 31) / threads / run * run;
+  for (uint64_t first = 0; first < b.count; first += most) {
+    const uint64_t n = std::min<uint64_t>(most, b.count - first);
+    b.first = (uint32_t)first;
+    launch(b, (uint32_t)((n + run - 1) / run * run));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Reduce-scatter
+// ---------------------------------------------------------------------------
+
+// Slots of a lane group: the sub-tree it walks spans at most 2^(slots - 1)
+// groups of positions.
+constexpr int walk_slots(int S) { return S <= 4 ? 6 : 8; }
+// Positions read at a time.  A whole tree: 4.  A part of one: float32 and
+// int32 2, bf16 4.  VGPRs of a part's kernels, with a chunk's own workgroups /
+// shared ones: float32 56 / 62-70 at 256 lanes, 64 / 70-78 at 1024; bf16 66 /
+// 74-82 and 74 / 79-90 (64 leave 8 waves per SIMD, 72 7, 80 6, 96 5).
+constexpr int walk_group(int elem, int S) { return S == 1 || elem == 2 ? 4 : 2; }
+
+// S: lane groups per vector.  One reads a whole tree where that alone gives
+// enough waves: walk_waves, about what keeps HBM busy.  Fewer leave it waiting,
+// more cost an LDS exchange per vector and shorter walks.  A group keeps at
+// least kWalkSpan positions (two to four rounds of loads), and at most what its
+// slots hold.  Measured on MI355X, us at S = 1, 2, 4, 8, 16 (waves at S = 1):
+//   float32  N=50 20 KB (976) 17, 14, 10.5, 10.5, 12; N=500 1200 B (585) -, -,
+//            61, 56, 64; N=100 40 KB (3906) 68, 65, 64, 69, 75; N=10 1 MiB
+//            (10240) 21, 24, 26, 37, 60
+//   bf16     N=64 32 KiB (4096) 24, 25, 24, 27, 48; N=24 64 KiB (3072) 8.4, 9.3,
+//            9.6, 14, 28; N=200 666 B (262) 30, 21, 12, 9.4, 10.9
+// A bf16 walk over rows off an 8-byte boundary, whose accesses are split, is
+// faster in two parts when it is large: N=64 262143 elements 503, 432 us.
+//
+// Workgroups of 256 lanes.  For large whole-tree walks wider ones are slower and
+// narrower ones no different, us at 256 lanes / at another width, side by side:
+//   N=64 float32 1 MiB    64: 653, 648   128: 657, 634   512: 640, 705   1024: 657, 700
+//   N=128 bf16 4 MiB, ms  64: 10.7, 10.6 128: 10.3, 10.5 512: 10.6, 10.7 1024: 10.7, 11.0
+//   N=64 float32 262143   64: 692, 682   128: 675, 687   512: 682, 745   1024: 681, 739
+// (two runs of one width differ by up to 4%, once 6%).
+//
+// Order of the workgroups: each XCD takes runs of `grain` consecutive blocks,
+// whose rows then cover its L2's channels evenly; one by one, blocks of 1 KiB
+// per row keep an XCD on the same few channels (N=64 bf16 32 KiB at S = 4 35
+// against 23 us).  Long runs also keep an XCD on fewer pages: N=128 bf16 4 MiB
+// 13.0 ms one by one, 12.0, 11.9, 11.8 ms with runs of 16, 64, 256; short ones
+// leave a small grid balanced (N=300 float32 4 KiB, 1200 blocks: 75 us with
+// runs of 4, 126 with 64).
+constexpr int64_t walk_waves(int elem) { return elem == 2 ? 2048 : 4096; }
+constexpr int kWalkSpan = 8;
+constexpr int kWalkMostGroups = 16;
+
+// Whether the parts of a tree are read in keyed orders.  Position q of chunk R
+// is at row (R + q) * spacing + R * chunk: with both sizes powers of two and
+// all workgroups at the same q, R and R + q fall on address bits that the
+// memory channels' hash seems to combine (inferred from the sizes below, no
+// counter shows it), and the reads crowd on few channels; a key per workgroup
+// spreads q.  Measured on MI355X for float32, plain / keyed order
+// at the S in use: N=128, 16 KiB chunks (2 MiB rows) 58.6 / 44.6 us, 8 KiB 28.1
+// / 24.1, 4 KiB 15.2 / 12.3; N=1024 256 B 50.8 / 45.9; N=64 4 KiB 6.6 / 6.0;
+// N=32 16 KiB 6.1 / 6.0.  Beyond, where a workgroup's neighbours cover the
+// channels by themselves, plain order is faster: N=64 32 KiB 24.1 / 25.0, N=256
+// 16 KiB (4 MiB rows) 168 / 171, N=64 1 MiB 625 / 668, N=1024 64 B (64 KiB
+// rows) 23.6 / 27.3; so it is for rows of other spacings (N=128 16000 B 42.3 /
+// 44.0, N=100 16 KiB 27.3 / 28.2) and for bf16 (N=128 16 KiB 46.8 / 53.1).
+inline bool walk_keyed(int N, int64_t chunk_bytes, const WalkRows& rows) {
+  auto pow2 = [](int64_t v) { return v > 0 && (v & (v - 1)) == 0; };
+  return rows.spaced && pow2(N) && pow2(rows.send_stride) && pow2(chunk_bytes) && chunk_bytes <= 16384 &&
+         rows.send_stride >= (256 << 10) && rows.send_stride <= (2 << 20);
+}
+
+// A reduce-scatter's launch.
+struct ReduceShape {
+  int S;        // lane groups per vector
+  int threads;  // per workgroup
+  int lanes;    // vectors per workgroup, a multiple of 64
+  int w;        // positions per lane group, a power of two
+  bool uni;     // a workgroup's vectors belong to one chunk
+  bool keyed;
+  uint32_t tiles;  // workgroups per chunk, where they belong to one
+  Blocks blocks;
+};
+
+// V: 4-element vectors per chunk; elem: bytes per element.  False: no such launch.
+inline bool reduce_shape(int N, int64_t V, int64_t chunk_bytes, int elem, const WalkRows& rows, ReduceShape* sh) {
+  int span = 1;
+  while (span < N) span *= 2;
+  const int64_t waves = (N * V + 63) / 64;
+  auto holds = [&](int S) { return span / S <= walk_group(elem, S) << (walk_slots(S) - 1); };
+  int S = 1;
+  while (S < kWalkMostGroups && ((waves * S < walk_waves(elem) && span / S > kWalkSpan) || !holds(S))) S *= 2;
+  const bool split_rows = elem == 2 && (!rows.aligned8 || chunk_bytes % 8);
+  if (split_rows && S == 1 && waves >= 16384 && span > kWalkSpan) S = 2;
+  if (!holds(S)) return false;
+  sh->S = S;
+  sh->threads = S <= 4 ? 256 : 64 * S;
+  sh->lanes = sh->threads / S;
+  sh->w = span / S;
+  const int64_t tiles = (V + sh->lanes - 1) / sh->lanes;
+  // A chunk's vectors fill its own workgroups unless that leaves too many lanes idle.
+  sh->uni = tiles * sh->lanes <= V + V / 8;
+  const int64_t blocks = sh->uni ? tiles * N : (N * V + sh->lanes - 1) / sh->lanes;
+  if (blocks > (int64_t(1) << 31)) return false;
+  sh->tiles = (uint32_t)tiles;
+  sh->blocks = {(uint32_t)blocks, blocks >= 16384 ? 64u : 4u, 0};
+  sh->keyed = walk_keyed(N, chunk_bytes, rows) && sh->w >= walk_group(elem, S);
+  return true;
+}
+
+// The vector of a workgroup's lane: vector v of destination chunk R.  False: none.
+PAT_BOTH bool own_vector(uint32_t blk, int lane, int lanes, uint32_t tiles, int64_t V, int* R, int64_t* v) {
+  *R = (int)(blk / tiles);
+  *v = (int64_t)(blk - (uint32_t)*R * tiles) * lanes + lane;
+  return *v < V;
+}
+// The same where chunks share workgroups.  They do only below 8 * lanes <= 2048
+// vectors, and there are at most kWalkMostRanks chunks: 32 bits hold every index.
+PAT_BOTH bool shared_vector(uint32_t blk, int lane, int lanes, int N, int64_t V, int* R, int64_t* v) {
+  const uint32_t f = blk * (uint32_t)lanes + (uint32_t)lane;
+  *R = (int)(f / (uint32_t)V);
+  *v = f - (uint32_t)*R * (uint32_t)V;
+  return f < (uint32_t)N * (uint32_t)V;
+}
+
+// ---------------------------------------------------------------------------
+// All-gather
+// ---------------------------------------------------------------------------
+
+constexpr int kGatherThreads = 256;
+constexpr int kGatherTile = kGatherThreads * 16;  // bytes
+
+// Receivers per workgroup: as many as make one round of workgroups
+// (kGatherBlocks, what the chip holds) out of a small operation, at most 4.
+// One receiver each costs a chain of dependent loads per vector (N=24 bf16 64
+// KiB: 1, 2, 3, 4, 6 receivers 15.2, 8.0, 7.9, 7.8, 8.1 us); more than 4 only
+// write more rows at once (N=300 float32 4 KiB: 4, 6, 8 receivers 56, 60, 60
+// us; N=1000 252 B: 39, 42, 44 us).  A tiny operation is best spread (N=13 bf16
+// 2002 B: 3.8, 4.1, 4.8 us at 1, 2, 4).
+constexpr int kGatherRun = 4;
+constexpr int64_t kGatherBlocks = 2048;
+
+// An all-gather's launch: tile `tile` of the concatenation to receivers r0, r0 +
+// period, ... (`run` of them).
+struct GatherShape {
+  int32_t period, run;
+  uint32_t tiles;
+  Blocks blocks;
+};
+
+// False: no such launch.
+inline bool gather_shape(int N, int64_t row_bytes, int64_t recv_stride, GatherShape* sh) {
+  // Rows a period apart start at the same offset from a line.  With too few
+  // rows for that to leave kGatherRun in a class, neighbours share a workgroup
+  // (N=37 float32 9999 elements, period 32: 13 us against 28 us apart).
+  sh->period = 1;
+  for (int64_t s = recv_stride % 128; s % 128; s += recv_stride % 128) ++sh->period;
+  if (sh->period * kGatherRun > N) sh->period = 1;
+  // a tile more for rows that start up to 127 bytes past a line
+  const int64_t tiles = (row_bytes + 127 + kGatherTile - 1) / kGatherTile;
+  sh->run = (int32_t)std::min<int64_t>(kGatherRun, (tiles * N + kGatherBlocks - 1) / kGatherBlocks);
+  const int64_t turns = ((N + sh->period - 1) / sh->period + sh->run - 1) / sh->run;
+  const int64_t blocks = tiles * turns * sh->period;
+  if (blocks > (int64_t(1) << 31)) return false;
+  sh->tiles = (uint32_t)tiles;
+  // Order: tiles of the same receivers follow each other.  Runs of them per
+  // XCD for large operations only (in place, one by one / runs of 256: N=128
+  // float32 1 MiB, 1.05 M blocks, 3080 / 2760 us; N=50 float32 400 KB 163 / 162
+  // us; N=300 float32 4 KiB, 22500 blocks, 51 / 65 us; but N=700 bf16 32 KiB
+  // 2530 / 2630 us).
+  sh->blocks = {(uint32_t)blocks, blocks >= (1 << 18) ? 256u : 1u, 0};
+  return true;
+}
+
+PAT_BOTH void gather_block(uint32_t blk, uint32_t tiles, int32_t period, int32_t run, uint32_t* tile, int* r0) {
+  const uint32_t g = blk / tiles;
+  *tile = blk - g * tiles;
+  const int turn = (int)g / period;
+  *r0 = (int)g - turn * period + turn * run * period;
+}
+
+// Order of the workgroups.  A panel of the concatenation (at most kCopyPanel
+// tiles, 2 MiB) goes to every receiver before the next panel, and an XCD takes
+// the same eighth of it for each of them: its L2 then serves the panel's reads
+// but the first.  Measured on MI355X, us with the tiles of four receivers in a
+// loop (walk_ag_kernel) / in this order: N=128 float32 1 MiB 2937 / 2449 (7.0
+// TB/s written), N=700 bf16 32 KiB 2745 / 2239, N=128 bf16 262143 elements 1470 /
+// 1178, N=50 float32 400 KB 177 / 142, N=8 bf16 1000001 elements 29 / 20, N=24
+// bf16 64 KiB 8.5 / 7.6.  With XCD runs that do not repeat from one receiver to
+// the next: 2600, 2333, 1231, 157, 33, 8.2.  A concatenation under
+// kCopyLeastPanels tiles is in every L2 soon; there longer runs across the
+// receivers' rows are faster (N=5000 float32 64 B: 220 against 267 us, loop 265;
+// N=1024 bf16 38 B 7.9, 11.4, 10.6; N=100 bf16 6666 B 10.9, 12.0, 14.0; N=1000
+// float32 256 B 39, 37, 42).
+constexpr int64_t kCopyPanel = 512;
+constexpr int64_t kCopyLeastPanels = 256;
+
+// The launch of an all-gather of one tensor's rows.
+struct CopyShape {
+  uint32_t panel;  // tiles that every receiver takes before the next ones
+  Blocks blocks;
+};
+
+// False: no such launch.
+inline bool copy_shape(int N, int64_t row_bytes, CopyShape* sh) {
+  // a tile more for rows that start up to 127 bytes past a line
+  const int64_t tiles = (row_bytes + 127 + kGatherTile - 1) / kGatherTile;
+  const int64_t panels = (tiles + kCopyPanel - 1) / kCopyPanel;
+  int64_t grain = ((tiles + panels - 1) / panels + 7) / 8;
+  sh->panel = (uint32_t)(8 * grain);
+  if (tiles < kCopyLeastPanels) {
+    sh->panel = (uint32_t)tiles;
+    grain = tiles * N >= 65536 ? 64 : 16;
+  }
+  const int64_t blocks = panels * sh->panel * N;
+  if (blocks > (int64_t(1) << 31)) return false;
+  sh->blocks = {(uint32_t)blocks, (uint32_t)grain, 0};
+  return true;
+}
+
+PAT_BOTH void copy_block(uint32_t blk, uint32_t panel, uint32_t N, uint32_t* tile, uint32_t* receiver) {
+  const uint32_t g = blk / panel, p = g / N;  // (panel, receiver, tile of the panel)
+  *tile = p * panel + (blk - g * panel);
+  *receiver = g - p * N;
+}
+
+}  // namespace pat

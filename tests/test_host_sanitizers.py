@@ -50,6 +50,23 @@ def test_abi_host_paths_under_asan_ubsan(tmp_path):
     assert "plans checked, 0 failures" in res.stdout
 
 
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include/hip"),
+                    reason="no g++ or no HIP headers")
+def test_walk_launches_under_asan_ubsan(tmp_path):
+    """How the walk kernels cut an operation into workgroups (walk_shape.hpp),
+    driven by tests/host/walk_check.cpp: every vector and every byte belongs to
+    exactly one lane, and a lane group's slots hold what it walks."""
+    exe = tmp_path / "walk_check"
+    csrc = os.path.join(ROOT, "paper_2506_20252_amd", "csrc")
+    cmd = ["g++", "-std=c++17", "-O2", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+           "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", csrc,
+           os.path.join(ROOT, "tests", "host", "walk_check.cpp"), "-o", str(exe)]
+    subprocess.run(cmd, check=True, capture_output=True, text=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=600)
+    assert res.returncode == 0, (res.stdout[-1000:], res.stderr[-2000:])
+    assert "launches checked, 0 failures" in res.stdout
+
+
 @pytest.fixture(scope="module")
 def call_check(tmp_path_factory):
     """The C-ABI layer over a stand-in for the HIP runtime (tests/host/hip_fake.hpp)."""
