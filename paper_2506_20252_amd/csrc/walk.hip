@@ -434,9 +434,9 @@ __global__ __launch_bounds__(kGatherThreads) void walk_ag_kernel(WalkArgs<Gather
   using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
   const uint32_t blk = block_of(cx.blocks, blockIdx.x);
   if (blk >= cx.blocks.count) return;
-  uint32_t tile;
-  int r0;  // receivers r0, r0 + period, ...: `run` of them
-  gather_block(blk, cx.tiles, cx.period, cx.run, &tile, &r0);
+  const uint32_t g = blk / cx.tiles, tile = blk - g * cx.tiles;
+  // receivers r0, r0 + period, ...: `run` of them
+  const int turn = (int)g / cx.period, r0 = (int)g - turn * cx.period + turn * cx.run * cx.period;
   if (r0 >= cx.N) return;
   const int64_t C = cx.chunk_bytes;
   const int64_t tile0 = (int64_t)tile * kGatherTile - (int64_t)((uintptr_t)recv_row<SPACED>(cx, r0) & 127);  // may be negative

@@ -207,13 +207,6 @@ inline bool gather_shape(int N, int64_t row_bytes, int64_t recv_stride, GatherSh
   return true;
 }
 
-PAT_BOTH void gather_block(uint32_t blk, uint32_t tiles, int32_t period, int32_t run, uint32_t* tile, int* r0) {
-  const uint32_t g = blk / tiles;
-  *tile = blk - g * tiles;
-  const int turn = (int)g / period;
-  *r0 = (int)g - turn * period + turn * run * period;
-}
-
 // Order of the workgroups.  A panel of the concatenation (at most kCopyPanel
 // tiles, 2 MiB) goes to every receiver before the next panel, and an XCD takes
 // the same eighth of it for each of them: its L2 then serves the panel's reads

@@ -84,9 +84,8 @@ static void check_gather(int N, int64_t row_bytes, int64_t at, int64_t stride) {
   EXPECT(g.run >= 1 && g.run <= kGatherRun && g.period >= 1);
   std::vector<uint8_t> seen(size_t(N) * row_bytes / 2);  // per two bytes: every size and offset is even
   all_blocks(g.blocks, kGatherThreads, [&](uint32_t blk) {
-    uint32_t tile;
-    int r0;
-    gather_block(blk, g.tiles, g.period, g.run, &tile, &r0);
+    const uint32_t group = blk / g.tiles, tile = blk - group * g.tiles;  // as walk_ag_kernel takes them apart
+    const int turn = (int)group / g.period, r0 = (int)group - turn * g.period + turn * g.run * g.period;
     EXPECT(tile < g.tiles && r0 >= 0);
     for (int k = 0, r = r0; k < g.run && r < N; ++k, r += g.period) cover(seen, r, tile, offset(r0));
   });
