@@ -305,7 +305,8 @@ pat_status_t pat_plan_info(pat_collective_t coll, int nranks, size_t count, pat_
 /* What an operation launches at the current settings (execution mode, fusion,
  * linear order, budget, environment, a trace of the schedule that is armed):
  * the decision the entry points make, for a plan that is made now.  For
- * pat_reducescatter_noalloc: in stream mode.  Host-only: needs no GPU. */
+ * pat_reducescatter_noalloc, which neither traces nor clocks its steps: the
+ * answer in stream mode without either.  Host-only: needs no GPU. */
 typedef struct {
   int walk;        /* 1: one walk launch; 0: the step schedule's launches (or nothing) */
   int launches;    /* kernels per operation (graph mode: in its graph); 0: none (one rank, an empty chunk).

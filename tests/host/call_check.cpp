@@ -143,8 +143,9 @@ static void check_routes() {
     int used = 0;
     EXPECT(pat_trace_read(nullptr, nullptr, nullptr, nullptr, 1, &used) == PAT_OK && used == (c.n > 1));
     for (const char* name : {"PAT_WALK", "PAT_TREE_TILE", "PAT_TREE_FUSE_VECS", "PAT_TREE_FUSE_BYTES",
-                             "PAT_TREE_EDGE_CACHE", "PAT_STREAMING", "PAT_STEP_CLOCK"}) {
-      EXPECT(pat_finalize() == PAT_OK);  // the step clock is a plan's
+                             "PAT_TREE_EDGE_CACHE", "PAT_STREAMING", "PAT_XCD_GRAIN", "PAT_PIECE_PIPELINE",
+                             "PAT_STEP_CLOCK"}) {
+      EXPECT(pat_finalize() == PAT_OK);  // some are a plan's
       setenv(name, std::strcmp(name, "PAT_STEP_CLOCK") ? "0" : "1", 1);
       agrees(c, false);
       unsetenv(name);
